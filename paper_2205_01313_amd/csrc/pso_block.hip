@@ -656,10 +656,10 @@ __device__ uint32_t staged_iterate(const SwarmArgs &a, const Staged &S, const Pa
         L.stop = meets_tol(L.gkey, tol, fstar);
         __syncthreads();
     };
-    // the clamp bounds in vector registers for the whole call (a select
+    // the position bounds in vector registers for the whole call (a select
     // between a lane value and a scalar operand costs a move per use)
     SwarmArgs lv = la;
-    asm volatile("" : "+v"(lv.vmax), "+v"(lv.lo), "+v"(lv.hi));
+    asm volatile("" : "+v"(lv.lo), "+v"(lv.hi));
     L.stop = L.stop || meets_tol(L.gkey, tol, fstar);
     if (PAIR && !split && npairs == 1) {
         // D <= 2: a lane takes its particles whole, the fitness summed in

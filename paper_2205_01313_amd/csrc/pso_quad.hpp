@@ -15,6 +15,15 @@ __device__ __forceinline__ float clampf(float v, float lo, float hi)
     return (v > hi) ? hi : v;
 }
 
+// clampf(v, -m, m) for m > 0 in two instructions instead of two compares and
+// two selects: v_maximum3_f32 and v_minimum3_f32 order like the comparisons
+// and pass a NaN on, as they do.  (Bounds that are zero would differ in the
+// sign of a zero result, so the position clamp keeps the comparisons.)
+__device__ __forceinline__ float clamp_sym(float v, float m)
+{
+    return __builtin_elementwise_minimum(__builtin_elementwise_maximum(v, -m), m);
+}
+
 typedef float f4 __attribute__((ext_vector_type(4)));
 
 // 16-byte accesses of lane quad q within one dimension's row.  An array
@@ -125,7 +134,7 @@ __device__ __forceinline__ float velocity_eq1_own(const SwarmArgs &a, float x, f
 
 __device__ __forceinline__ float velocity_eq1_social(const SwarmArgs &a, float own, float c2r2, float x, float g)
 {
-    return clampf(own + (c2r2 * (g - x)), -a.vmax, a.vmax);
+    return clamp_sym(own + (c2r2 * (g - x)), a.vmax);
 }
 
 __device__ __forceinline__ float velocity_eq1(const SwarmArgs &a, float x, float v, float p, float g, float r1, float r2)
