@@ -132,15 +132,18 @@ int pso_step(pso_swarm *s);
  * Blocks until done, then writes the gbest fitness, the gbest position
  * (D floats, host), the iteration at which the gbest last changed (0 = at
  * initialisation) and the number of iterations this call ran.  Any output
- * pointer may be NULL.  A synchronous swarm with N*D <= 65536 whose state
- * fits one workgroup's LDS runs the whole call as one launch of one
- * workgroup (its state staged in LDS), unless N >= 4096 or N*D >= 8192 and
- * the gang below has 8 parts or more; a synchronous swarm with D <= 16 that
- * does not take it runs the call as one launch of ceil(N / 256) co-resident
- * workgroups (2 to 256), each holding a slice in LDS and meeting the others
- * once per iteration (PSO_GANG=0 in the environment turns this off; a part
- * that waits past 20 s sets a device error, returned as PSO_EDEVICE); others
- * take one launch per iteration (PSO_PERSISTENT: one persistent launch).
+ * pointer may be NULL.  A synchronous swarm that fits the device's vector
+ * registers and LDS (N*D up to about 8 million, D <= 512, N <= 262144) runs
+ * as launches of up to 256 co-resident workgroups (about 50 ms each) that
+ * keep it there and meet once per iteration, or once per block of iterations
+ * while the gbest does not change.  If the workgroups are not resident
+ * together within 2 ms (another kernel holds the device) nothing has run and
+ * the call goes on as below; a workgroup that is lost later (20 s) sets a
+ * device error, returned as PSO_EDEVICE.  PSO_GANG=0 in the environment turns
+ * this off.  Else a synchronous swarm with N*D <= 65536 whose state fits one
+ * workgroup's LDS runs the whole call as one launch of one workgroup, and
+ * others take one launch per iteration (PSO_PERSISTENT: one persistent
+ * launch).
  * Every path computes the same bits. */
 int pso_run(pso_swarm *s, int64_t max_iter, float tol, float f_star, float *gbest_value,
             float *gbest_pos_host, int64_t *gbest_iter, int64_t *iters_done);

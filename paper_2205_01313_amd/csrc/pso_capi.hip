@@ -17,6 +17,7 @@
 
 #include "pso.h"
 #include "pso_block.hpp"
+#include "pso_gang.hpp"
 #include "pso_guard.hpp"
 #include "pso_device.hpp"
 #include "pso_kernels.hpp"
@@ -61,7 +62,8 @@ constexpr uint64_t MAX_BATCH_BYTES = uint64_t(1) << 52;
 // workgroup / launches: Cubic 1D N = 16 384: 19.0 / 5.3, N = 8192: 9.7 /
 // 5.2; Rastrigin D = 8, N = 2048: 13.7 / 10.7; D = 128, N = 512: 99.8 /
 // 14.0; Ackley D = 32, N = 1024: 26.2 / 9.8), so it runs only under
-// PSO_BLOCK_STAGED=0 (tests compare the two one-workgroup kernels).
+// PSO_BLOCK_STAGED=0 (tests compare the two one-workgroup kernels).  The
+// resident gang takes every swarm it accepts before either (gang_run).
 #ifndef PSO_BLOCK_RUN_MAX_ND
 #define PSO_BLOCK_RUN_MAX_ND 65536
 #endif
@@ -105,7 +107,9 @@ struct pso_swarm {
     hipGraph_t steps_graph = nullptr;
     hipGraphExec_t steps_exec = nullptr;
     int steps_key = -1;
-    // the gang run's meeting words (allocated at its first run)
+    float shift_max = 0.0f; // largest magnitude of the shift vector
+    bool state_set = false; // the state came from pso_set_state
+    // the gang's meeting words (allocated at its first run)
     unsigned long long *gang_words = nullptr;
     size_t gang_words_n = 0;
 };
@@ -265,9 +269,13 @@ int pso_set_shift(pso_swarm *s, const float *shift_host)
                 h[d] = shift_host[d];
             }
         }
+        float m = 0.0f;
+        for (float v : h) m = std::max(m, std::fabs(v));
+        s->shift_max = m;
         HIP_TRY(hipMemcpyAsync(const_cast<float *>(s->args.shift), h.data(), sizeof(float) * s->D,
                                hipMemcpyHostToDevice, s->stream));
         HIP_TRY(hipStreamSynchronize(s->stream)); // h is a stack buffer
+        s->state_set = false;
         return enqueue_init(s);
     });
 }
@@ -296,6 +304,7 @@ int pso_reset(pso_swarm *s)
 {
     return pso::guarded([&]() -> int {
         if (!s) return fail(PSO_EINVAL, "swarm is NULL");
+        s->state_set = false;
         return enqueue_init(s);
     });
 }
@@ -361,6 +370,52 @@ int enqueue_steps(pso_swarm *s, int64_t n)
     return PSO_OK;
 }
 
+// Runs the swarm's next iterations as a resident gang where that suits it,
+// and takes what it ran off *left (the rest is for the other paths).  The
+// stop rule is armed; *fetched: the host's copies of the control block and the
+// gbest position are those of the run's end.  A launch is kept to about
+// GANG_LAUNCH_US (an iteration takes at most about 1 us and 2.5 us per million
+// particle-dimensions) so that other work on the device waits no longer for
+// its compute units.
+constexpr double GANG_LAUNCH_US = 50000.0;
+
+int gang_run(pso_swarm *s, int64_t *left, bool *fetched)
+{
+    pso::GangShape sh;
+    // a path forced from the environment is meant
+    for (const char *name : {"PSO_STEP_SPLIT", "PSO_STEP_ONE", "PSO_SPLIT_PHASES", "PSO_RUN_GRAPH", "PSO_BLOCK_STAGED"})
+        if (getenv(name)) return PSO_OK;
+    if (!pso::gang_accepts(s->fitness, s->args, s->shift_max, s->state_set) ||
+        !pso::gang_shape(s->fitness, s->args, &sh))
+        return PSO_OK;
+    const size_t n = pso::gang_words(sh.G, s->D);
+    if (n > s->gang_words_n) {
+        HIP_TRY(hipStreamSynchronize(s->stream));
+        if (s->gang_words) (void)hipFree(s->gang_words);
+        s->gang_words = nullptr;
+        s->gang_words_n = 0;
+        if (hipMalloc(reinterpret_cast<void **>(&s->gang_words), n * sizeof(unsigned long long)) != hipSuccess) {
+            s->gang_words = nullptr;
+            (void)hipGetLastError();
+            return PSO_OK; // the other paths need no more memory
+        }
+        s->gang_words_n = n;
+    }
+    const int64_t most = std::max<int64_t>(64, std::min<int64_t>(pso::GANG_MAX_T, int64_t(GANG_LAUNCH_US / (1.0 + 2.5e-6 * double(s->N) * s->D))));
+    for (bool first = true; *left > 0; first = false) {
+        const int64_t T = std::min(*left, most);
+        if (!first) HIP_TRY(pso::launch_gang_arm(s->args, s->stream));
+        HIP_TRY(pso::launch_gang(s->args, sh, (uint32_t)T, s->gang_words, s->stream));
+        int rc = fetch_ctrl(s, true);
+        if (rc) return rc;
+        if (s->host_ctrl->gang_state == pso::GANG_ABSENT) break;
+        *left -= T;
+        if (s->host_ctrl->stop) *left = 0;
+    }
+    *fetched = *left == 0;
+    return PSO_OK;
+}
+
 // Persistent launches for T iterations (each clears its iteration counts).
 int persistent_launch(pso_swarm *s, int64_t T)
 {
@@ -393,38 +448,22 @@ int pso_run(pso_swarm *s, int64_t max_iter, float tol, float f_star, float *gbes
         if (max_iter < 0) return fail(PSO_EINVAL, "max_iter < 0");
         if (std::isnan(tol) || std::isnan(f_star)) return fail(PSO_EINVAL, "tol and f_star must not be NaN");
         HIP_TRY(pso::launch_arm(s->args, tol, f_star, s->stream));
-        bool block_path = s->variant == PSO_SYNC && int64_t(s->N) * s->D <= BLOCK_RUN_MAX_ND &&
-                          pso::block_run_suits(s->fitness, s->args);
-        uint32_t gang_parts = s->variant == PSO_SYNC ? pso::gang_run_parts(s->fitness, s->args) : 0u;
-        if (block_path) {
-            // a gang of 8 or more parts meets in about 2 us per iteration and
-            // overtakes one workgroup from N = 4096 or N*D = 8192 (Cubic 1D
-            // N = 4096: 2.34 against 2.85 us; Rastrigin D = 4, N = 2048: 3.38
-            // against 5.71; below, one workgroup: D = 2, N = 2048 2.00 against 2.25)
-            const bool gang_first = gang_parts >= 8 && (s->N >= 4096 || int64_t(s->N) * s->D >= 8192);
-            if (gang_first)
-                block_path = false;
-            else
-                gang_parts = 0;
+        bool fetched = false;
+        if (s->variant == PSO_SYNC && max_iter > 0) {
+            // the gang runs what it can; max_iter keeps what is left for the
+            // other paths (all of it where its parts were not resident)
+            int rc = gang_run(s, &max_iter, &fetched);
+            if (rc) return rc;
         }
-        if (s->variant == PSO_PERSISTENT) {
+        const bool block_path = s->variant == PSO_SYNC && int64_t(s->N) * s->D <= BLOCK_RUN_MAX_ND &&
+                                pso::block_run_suits(s->fitness, s->args);
+        if (fetched) {
+            // the gang ran it all
+        } else if (s->variant == PSO_PERSISTENT) {
             int rc = persistent_launch(s, max_iter);
             if (rc) return rc;
         } else if (block_path) {
             if (max_iter > 0) HIP_TRY(pso::launch_block_run(s->fitness, s->args, max_iter, s->stream));
-        } else if (gang_parts > 0) {
-            const size_t n = pso::gang_run_words(gang_parts, s->D);
-            if (n > s->gang_words_n) {
-                HIP_TRY(hipStreamSynchronize(s->stream));
-                if (s->gang_words) (void)hipFree(s->gang_words);
-                s->gang_words = nullptr;
-                s->gang_words_n = 0;
-                if (hipMalloc(reinterpret_cast<void **>(&s->gang_words), n * sizeof(unsigned long long)) != hipSuccess)
-                    return fail(PSO_ENOMEM, "gang meeting words: device allocation failed");
-                s->gang_words_n = n;
-            }
-            if (max_iter > 0)
-                HIP_TRY(pso::launch_gang_run(s->fitness, s->args, max_iter, gang_parts, s->gang_words, s->stream));
         } else if (tol > 0.0f) {
             // Chunks of iterations with one chunk always queued ahead; the
             // device skips iterations once the stop rule holds, and the host
@@ -474,7 +513,7 @@ int pso_run(pso_swarm *s, int64_t max_iter, float tol, float f_star, float *gbes
             int rc = enqueue_steps(s, max_iter);
             if (rc) return rc;
         }
-        int rc = fetch_ctrl(s, true);
+        int rc = fetched ? PSO_OK : fetch_ctrl(s, true);
         if (rc) return rc;
         const Ctrl &c = *s->host_ctrl;
         if (gbest_value) *gbest_value = pso::key_fitness(c.gkey_prev);
@@ -552,6 +591,7 @@ int pso_set_state(pso_swarm *s, const float *x_host, const float *v_host, const 
             return fail(PSO_EINVAL, "bad iteration counters");
         if ((gbest_key & 0xFFFFFFFFull) >= s->N) return fail(PSO_EINVAL, "gbest index out of range");
         HIP_TRY(hipStreamSynchronize(s->stream));
+        s->state_set = true;
         const size_t row = sizeof(float) * s->N, pitch = sizeof(float) * s->L.Np;
         HIP_TRY(hipMemcpy2D(s->args.x, pitch, x_host, row, row, s->D, hipMemcpyHostToDevice));
         HIP_TRY(hipMemcpy2D(s->args.v, pitch, v_host, row, row, s->D, hipMemcpyHostToDevice));

@@ -175,6 +175,8 @@ __global__ void k_reset(SwarmArgs a)
     c->tiles = 0;
     c->fresh = 0;
     c->arrive = 0;
+    c->gang_arrive = 0;
+    c->gang_state = 0;
     c->gkey_prev = NO_KEY;
     c->giter = 0;
     c->t = 0;
@@ -197,7 +199,16 @@ __global__ void k_arm(SwarmArgs a, float tol, float fstar)
     c->tol = tol;
     c->fstar = fstar;
     c->t_run0 = c->t;
+    c->gang_arrive = 0;
+    c->gang_state = 0;
     c->stop = (tol > 0.0f && __builtin_fabsf(key_fitness(c->gkey_prev) - fstar) < tol) ? 1u : 0u;
+}
+
+__global__ void k_gang_arm(SwarmArgs a)
+{
+    if (threadIdx.x != 0) return;
+    a.ctrl->gang_arrive = 0;
+    a.ctrl->gang_state = 0;
 }
 
 // ---------------------------------------------------------------------------
@@ -886,6 +897,12 @@ hipError_t launch_reset(const SwarmArgs &a, hipStream_t stream)
 hipError_t launch_arm(const SwarmArgs &a, float tol, float fstar, hipStream_t stream)
 {
     hipLaunchKernelGGL(k_arm, dim3(1), dim3(64), 0, stream, a, tol, fstar);
+    return hipGetLastError();
+}
+
+hipError_t launch_gang_arm(const SwarmArgs &a, hipStream_t stream)
+{
+    hipLaunchKernelGGL(k_gang_arm, dim3(1), dim3(64), 0, stream, a);
     return hipGetLastError();
 }
 

@@ -22,7 +22,9 @@ struct alignas(256) Ctrl {
     unsigned char pad0[224];
     // line 1: workgroups that finished the current launch
     unsigned int arrive;
-    unsigned char pad1[252];
+    // resident gang: parts that reached a launch's rendezvous, and its outcome
+    unsigned int gang_arrive, gang_state;
+    unsigned char pad1[244];
     // line 2: bookkeeping, written by the last workgroup of each launch
     unsigned long long gkey_prev; // gbest key after the previous iteration
     long long giter;              // iteration at which the gbest last changed
@@ -107,6 +109,9 @@ hipError_t launch_step(int fitness, int variant, const SwarmArgs &a, hipStream_t
 // (PSO_ASYNC_TILES in the environment, 1..64; default 2).
 uint32_t async_tiles_per_workgroup();
 hipError_t launch_arm(const SwarmArgs &a, float tol, float fstar, hipStream_t stream);
+// Clears the gang's rendezvous fields before each gang launch after the first
+// (launch_arm clears them too).
+hipError_t launch_gang_arm(const SwarmArgs &a, hipStream_t stream);
 // Copies every pending pbest position from x to p (before the state is read).
 hipError_t launch_flush(const SwarmArgs &a, hipStream_t stream);
 // Marks no pbest position pending (after the state is replaced).

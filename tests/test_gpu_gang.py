@@ -1,0 +1,160 @@
+"""The resident gang behind pso_run: every instantiation at the edges of its
+shapes (one part and many, particles past the last part's, dimensions past the
+last chunk's, two to sixteen lanes per particle), bit for bit against the
+oracle -- state, history, improvement count, continued runs, stop rule --;
+parameters at the limits of what it accepts; and gangs that cannot all be
+resident together."""
+import threading
+
+import numpy as np
+import pytest
+
+import paper_2205_01313_amd as pso
+from paper_2205_01313_amd import workloads as wl
+from tests.gpu_util import announce, assert_state_equal, gpu_swarm, oracle_swarm
+
+pytestmark = pytest.mark.gpu
+
+
+def run_parts(g, cuts, tol=0.0, f_star=0.0):
+    r = None
+    for n in cuts:
+        r = g.run(n, tol=tol, f_star=f_star)
+    return r
+
+
+def check(spec, cuts, tol=0.0, f_star=0.0):
+    T = sum(cuts)
+    with gpu_swarm(spec) as g:
+        r = run_parts(g, cuts, tol, f_star)
+        st = g.state()
+        hist = g.history(0, st["t"] + 1)
+        imp = g.counters()["pbest_improvements"]
+    o = oracle_swarm(spec, 8).run_f32(T, tol=tol, f_star=f_star)
+    assert st["t"] == o["iters"] and r["gbest_fit"] == o["gbest_fit"] and r["gbest_iter"] == o["giter"]
+    assert np.array_equal(hist, o["hist"])
+    assert_state_equal(st, o, spec.N, spec.D)
+    return imp, st, hist
+
+
+# "C,P": dimensions of a lane, particles of a part
+@pytest.mark.parametrize("fit,N,D,shape", [
+    ("sphere", 1, 1, "2,64"), ("cubic", 65, 1, "2,64"), ("rastrigin", 1000, 2, "2,256"), ("ackley", 4001, 2, "2,1024"),
+    ("rosenbrock", 257, 3, "4,256"), ("sphere", 700, 7, "8,512"), ("cubic", 1025, 8, "8,1024"),
+    ("rastrigin", 900, 13, "16,512"), ("ackley", 1500, 16, "16,1024"), ("rosenbrock", 1100, 31, "32,1024"),
+    ("sphere", 600, 63, "64,512"), ("rastrigin", 130, 3, "2,64"), ("rosenbrock", 200, 9, "2,128"),
+    ("ackley", 321, 17, "4,64"), ("rosenbrock", 500, 33, "8,64"), ("cubic", 64, 65, "8,64"),
+    ("rastrigin", 129, 47, "16,128"), ("rosenbrock", 70, 18, "16,64"), ("sphere", 33, 31, "2,16"),
+    ("rosenbrock", 50, 21, "2,32"), ("ackley", 95, 13, "4,32"), ("rastrigin", 40, 101, "8,16"),
+    ("rosenbrock", 47, 70, "8,32"), ("rosenbrock", 300, 127, "64,256"), ("ackley", 300, 66, "64,256"),
+    ("cubic", 130, 129, "64,64"), ("rastrigin", 129, 125, "64,128")])
+def test_gang_shapes_equal_oracle(monkeypatch, fit, N, D, shape):
+    spec = wl.SwarmSpec(fit, N, D, 60, seed=N * 3 + D, shift_amplitude=1.5)
+    announce(f"gang {fit} N={N} D={D} shape {shape}")
+    monkeypatch.setenv("PSO_GANG_SHAPE", shape)
+    imp, st, hist = check(spec, (1, 24, 35))
+    monkeypatch.delenv("PSO_GANG_SHAPE")
+    monkeypatch.setenv("PSO_GANG", "0")
+    imp0, st0, hist0 = check(spec, (60,))
+    assert imp == imp0 and np.array_equal(hist, hist0)
+
+
+@pytest.mark.parametrize("fit,N,D,tol", [("sphere", 300, 1, 1e-6), ("sphere", 5000, 2, 1e-8), ("rastrigin", 2000, 3, 1e-3),
+                                         ("ackley", 700, 5, 1e-3), ("sphere", 3000, 12, 1e-3), ("sphere", 513, 20, 1.0)])
+def test_gang_blocks_and_stop_rule(fit, N, D, tol):
+    """Long enough for the blocks of iterations to grow (the gbest settles),
+    with a stop rule that is met inside one."""
+    spec = wl.SwarmSpec(fit, N, D, 900, seed=5 * N + D, shift_amplitude=1.0)
+    announce(f"gang stop rule {fit} N={N} D={D}")
+    check(spec, (7, 893), tol=tol)
+    check(spec, (400, 500))
+
+
+@pytest.mark.parametrize("name,kw", [
+    ("no cognitive term", dict(c1=0.0)), ("tiny c1", dict(c1=1e-33)), ("smallest c2", dict(c2=1e-38)),
+    ("lower bound 0", dict(box=(0.0, 7.0), vmax=0.7)), ("upper bound -0", dict(box=(-7.0, -0.0), vmax=0.7)),
+    ("lower bound -0", dict(box=(-0.0, 7.0), vmax=3.0)), ("wide box", dict(box=(-3e6, 3e6), vmax=6e5)),
+    ("infinite velocities", dict(w=3e38, vmax=1e4))])
+@pytest.mark.parametrize("fit", ["rastrigin", "sphere"])
+def test_gang_parameter_limits(monkeypatch, fit, name, kw):
+    spec = wl.SwarmSpec(fit, 700, 6, 40, seed=11, **kw)
+    announce(f"gang limits {fit}: {name}")
+    imp, st, hist = check(spec, (15, 25))
+    monkeypatch.setenv("PSO_GANG", "0")
+    imp0, st0, hist0 = check(spec, (40,))
+    assert imp == imp0
+    # a state the caller set: zeros of both signs and a pbest outside the box
+    with gpu_swarm(spec) as g:
+        st0 = g.state()
+        st0["x"][::3] = -0.0
+        st0["v"][::3] = -0.0
+        st0["p"][::5] = np.float32(1e3)
+        out = []
+        for env in ("0", None):
+            monkeypatch.setenv("PSO_GANG", env) if env else monkeypatch.delenv("PSO_GANG")
+            g.set_state(st0)
+            g.run(20)
+            out.append(g.state())
+    for k in ("x", "v", "p", "pf"):
+        assert np.array_equal(out[0][k].view(np.uint32), out[1][k].view(np.uint32)), k
+
+
+def test_gangs_that_exclude_each_other(monkeypatch):
+    """Several swarms whose gangs each want most compute units, run from
+    several threads at once: whichever parts are not resident together in time
+    leave the state alone and the step launches run instead."""
+    specs = [wl.SwarmSpec("rosenbrock", 65536, 40, 30, seed=s) for s in range(3)]
+    monkeypatch.setenv("PSO_GANG", "0")
+    want = []
+    for sp in specs:
+        with gpu_swarm(sp) as g:
+            g.run(sp.T)
+            want.append(g.state())
+    monkeypatch.delenv("PSO_GANG")
+    swarms = [gpu_swarm(sp) for sp in specs]
+    try:
+        for _ in range(2):
+            for g in swarms:
+                g.reset()
+            errs = []
+
+            def go(g, sp):
+                try:
+                    g.run(sp.T // 2)
+                    g.run(sp.T - sp.T // 2)
+                except Exception as e:  # noqa: BLE001 - reported below
+                    errs.append(e)
+
+            ts = [threading.Thread(target=go, args=a) for a in zip(swarms, specs)]
+            [t.start() for t in ts]
+            [t.join() for t in ts]
+            assert not errs
+            for g, w in zip(swarms, want):
+                st = g.state()
+                assert st["t"] == w["t"] and st["gkey"] == w["gkey"]
+                for k in ("x", "v", "p", "pf"):
+                    assert np.array_equal(st[k].view(np.uint32), w[k].view(np.uint32)), k
+    finally:
+        for g in swarms:
+            g.close()
+
+
+def test_gang_on_the_callers_stream():
+    """pso_create_in: the caller's memory and stream, next to other work of
+    that stream."""
+    import torch
+
+    spec = wl.SwarmSpec("ackley", 3000, 30, 50, seed=4, shift_amplitude=2.0)
+    st = torch.cuda.Stream()
+    ws = torch.zeros(pso.pso_workspace_bytes(spec.N, spec.D) + 256, dtype=torch.uint8, device="cuda")
+    torch.cuda.synchronize()
+    off = (-ws.data_ptr()) % 256
+    with torch.cuda.stream(st):
+        a = torch.randn(512, 512, device="cuda")
+        with pso.Swarm(spec.fitness, spec.N, spec.D, spec.box, spec.w, spec.c1, spec.c2, spec.vmax, spec.seed,
+                       shift=spec.shift, workspace=ws[off:], stream=st) as g:
+            b = a @ a
+            g.run(spec.T)
+            s = g.state()
+            assert torch.equal(b, a @ a)
+    assert_state_equal(s, oracle_swarm(spec, 8).run_f32(spec.T), spec.N, spec.D)
