@@ -25,10 +25,15 @@ struct U4 {
     uint32_t a, b, c, d;
 };
 
-// a ^ b ^ c in one instruction (gfx950: truth table 0x96 of v_bitop3_b32).
+// a ^ b ^ c in one instruction (gfx950: truth table 0x96 of v_bitop3_b32; a
+// host compiler that reads this header has no such builtin).
 __device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t c)
 {
+#if defined(__HIP_DEVICE_COMPILE__)
     return __builtin_amdgcn_bitop3_b32(a, b, c, 0x96);
+#else
+    return a ^ b ^ c;
+#endif
 }
 
 __device__ __forceinline__ U4 philox4x32_10(uint32_t k0, uint32_t k1, uint32_t c0, uint32_t c1, uint32_t c2,
