@@ -116,7 +116,7 @@ struct OwnHalf { // of the next iteration: (w v) + ((c1 r1)(p - x)) and c2 r2
     float own[C], soc[C];
 };
 
-// Dimensions are taken in groups of four (two for C = 2): a group is skipped
+// Dimensions are taken in groups of four (all of C < 4): a group is skipped
 // whole past D, and otherwise computed whole -- two independent Philox draws
 // in straight-line code; dimensions of it past D hold values that nothing
 // reads.
@@ -137,7 +137,7 @@ __device__ __forceinline__ void own_half(const SwarmArgs &a, const GangArgs &ga,
         for (int c = e; c < e + Q; c += 2) {
             const U4 u = philox4x32_10(a.k0, a.k1, (uint32_t)(d0 + c) >> 1, i, t, TAG_VEL);
 #pragma unroll
-            for (int h = 0; h < 2; ++h) {
+            for (int h = 0; h < (C == 1 ? 1 : 2); ++h) {
                 const float r1 = (float)(word_r1(u, h) >> 8), r2 = (float)(word_r2(u, h) >> 8);
                 O.own[c + h] = (a.w * S.v[c + h]) + ((ga.c1s * r1) * (S.p[c + h] - S.x[c + h]));
                 O.soc[c + h] = ga.c2s * r2;
@@ -164,7 +164,7 @@ __global__ void __launch_bounds__(MAXT) k_gang_resident(SwarmArgs a, GangArgs ga
     constexpr int W = Fitness<FIT>::STAGE_WORDS;
     constexpr int Q = group_of(C), PR = C - PL, FK = TAIL ? 1 : 0; // FK: the chunk whose lanes fold
     constexpr bool STAGE = MULTI && !TAIL;
-    static_assert(C % 2 == 0 && C >= 2, "chunks hold whole Philox pairs");
+    static_assert((C == 1 && !MULTI) || C % 2 == 0, "chunks hold whole Philox pairs");
     static_assert(!TAIL || (MULTI && FIT == F_ACKLEY), "one word of two recomputed");
     __shared__ GangShared sh;
     // gbest position (two of them: a repeated block still reads the old one)
@@ -257,7 +257,7 @@ __global__ void __launch_bounds__(MAXT) k_gang_resident(SwarmArgs a, GangArgs ga
 
     float *s_g = s_gpos, *s_gn = s_gpos + DL; // in use, and the next one
     constexpr bool AHEAD = C <= 16 && PL == 0; // room for the next iteration's own half in registers
-    OwnHalf<AHEAD ? C : 2> O;
+    OwnHalf<AHEAD ? C : 1> O;
     bool have_own = false;
 
     // Steps 2-4 of iteration t; cand: this lane's particle improved and beats
@@ -288,7 +288,7 @@ __global__ void __launch_bounds__(MAXT) k_gang_resident(SwarmArgs a, GangArgs ga
                 U4 u{};
                 if constexpr (!AHEAD) u = philox4x32_10(a.k0, a.k1, (uint32_t)(d0 + q) >> 1, i, t, TAG_VEL);
 #pragma unroll
-                for (int h = 0; h < 2; ++h) {
+                for (int h = 0; h < (C == 1 ? 1 : 2); ++h) {
                     const int c = q + h, d = d0 + c;
                     float own, soc;
                     if constexpr (AHEAD) {
@@ -442,7 +442,7 @@ __global__ void __launch_bounds__(MAXT) k_gang_resident(SwarmArgs a, GangArgs ga
         const uint32_t tb = (uint32_t)(t0 + done);
         const int n = SPEC ? (int)min((long long)K, (long long)ga.T - done) : 1;
         int slot = (int)(seq % 3);
-        LaneState<SPEC ? C : 2, PL> B;
+        LaneState<SPEC ? C : 1, PL> B;
         if constexpr (SPEC) {
             if (n > 1) B = S;
         }
@@ -692,6 +692,7 @@ static const GangKernel *gang_table(int *n)
 {
     constexpr bool two = Fitness<FIT>::STAGE_WORDS == 2;
     static const GangKernel t[] = {
+        gang_entry<FIT, 1, false, true, true, 1024>(),
         gang_entry<FIT, 2, false, true, true, 1024>(),
         gang_entry<FIT, 4, false, true, true, 1024>(),
         gang_entry<FIT, 8, false, true, true, 512>(),
@@ -779,7 +780,8 @@ static bool gang_layout(int fitness, const SwarmArgs &a, int C, uint32_t P, Gang
 //     N = 32: D = 16 1.63 / 2.3 / 1.56, D = 64 2.75 / 3.2 / 2.76; N = 128:
 //     D = 8 1.47 / 2.4 / 1.63, D = 24 2.55 / 3.5 / 2.62; beyond, several:
 //     N = 300: D = 16 3.2 / 3.6 / 3.62; N = 200: D = 50 4.3 / 6.9 / 6.98
-//   D <= 2: 256 particles of a part: N = 16384, D = 1 0.87 / 0.89 / 5.61
+//   D <= 2: 256 particles of a part, one lane each (C = 1 for D = 1): N =
+//     16384, D = 2 1.05 / 1.08 / 6.27
 //   D <= 4: pairs of lanes with few particles each, 32 of a part, below N =
 //     6000 (2000, 3: 1.65 / 1.72 / 4.85), one lane beyond (8000, 4: 1.92 /
 //     1.97 / 7.83)
@@ -799,18 +801,18 @@ bool gang_shape(int fitness, const SwarmArgs &a, GangShape *out)
 {
     if (const char *env = getenv("PSO_GANG_SHAPE")) { // "C,P": forced (tests, measurements)
         int c = 0, p = 0;
-        return sscanf(env, "%d,%d", &c, &p) == 2 && c >= 2 && p >= 16 && p <= 1024 &&
+        return sscanf(env, "%d,%d", &c, &p) == 2 && c >= 1 && p >= 16 && p <= 1024 &&
                gang_layout(fitness, a, c, (uint32_t)p, out);
     }
     const int D = a.D;
     const uint32_t N = a.N;
     if (N <= 512 && (uint64_t)N * D <= 4096) {
         const uint32_t P = N <= 32 && D > 2 ? 32 : (N + 63) / 64 * 64;
-        for (int c = 2; c <= 8; c *= 2)
+        for (int c = D == 1 ? 1 : 2; c <= 8; c *= 2)
             if (P * ((uint32_t)(D + c - 1) / c) <= (D <= 4 ? 1024u : 768u) && gang_layout(fitness, a, c, P, out))
                 return true;
     }
-    int c = 2;
+    int c = D == 1 ? 1 : 2;
     uint32_t pmin = 256;
     if (D > 64) c = 8, pmin = 16;
     else if (D > 16) c = 8, pmin = 64;
