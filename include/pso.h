@@ -221,14 +221,14 @@ int pso64_step(pso_swarm64 *s);
  * (tol <= 0: off; tested before the first and after every iteration);
  * blocks.  Outputs (each may be NULL, host): gbest fitness, position (D
  * doubles), iteration of the last gbest change, iterations run.  A swarm
+ * that fits the device's vector registers (N*D up to about 4 million, D <=
+ * 256, N <= 262144) runs as launches of up to 256 co-resident workgroups as in
+ * pso_run (not resident together within 2 ms: the paths below).  Else a swarm
  * with D >= 32 and N <= 32768 launches one grid step per iteration (lanes
  * share each particle's dimensions); else a swarm whose x, v, p and pbest
  * fitness fit one workgroup's LDS ((3D+1)*N doubles, up to about 160 KiB)
- * runs in one workgroup (one launch, the state loaded once and stored back
- * at the end), unless D <= 8 and N >= 4096; a swarm with D <= 8 that does
- * not run there runs as one persistent launch of co-resident workgroups that
- * meet once per iteration, as does one with D < 32 whose workgroups can hold
- * their slices of the swarm in LDS; others launch one grid step per
+ * runs in one workgroup; else one with D <= 8 runs as one persistent launch of
+ * co-resident workgroups; others launch one grid step per
  * iteration.  Every path gives the same results. */
 int pso64_run(pso_swarm64 *s, int64_t max_iter, double tol, double f_star, double *gbest_value, double *gbest_pos,
               int64_t *gbest_iter, int64_t *iters_done);

@@ -386,7 +386,7 @@ int gang_run(pso_swarm *s, int64_t *left, bool *fetched)
     for (const char *name : {"PSO_STEP_SPLIT", "PSO_STEP_ONE", "PSO_SPLIT_PHASES", "PSO_RUN_GRAPH", "PSO_BLOCK_STAGED"})
         if (getenv(name)) return PSO_OK;
     if (!pso::gang_accepts(s->fitness, s->args, s->shift_max, s->state_set) ||
-        !pso::gang_shape(s->fitness, s->args, &sh))
+        !pso::gang_shape(s->fitness, s->args, *left, &sh))
         return PSO_OK;
     const size_t n = pso::gang_words(sh.G, s->D);
     if (n > s->gang_words_n) {

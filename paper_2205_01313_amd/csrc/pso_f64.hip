@@ -26,6 +26,8 @@
 #include "pso.h"
 #include "pso_device.hpp"
 #include "pso_f64.hpp"
+#include "pso_f64_device.hpp"
+#include "pso_gang.hpp"
 #include "pso_guard.hpp"
 #include "pso_kernels.hpp"
 
@@ -35,7 +37,6 @@ int pso_internal_check_desc(const pso_desc *d);
 namespace pso {
 
 constexpr int BLOCK64 = 256;
-constexpr uint32_t NO_IDX = 0xFFFFFFFFu;
 constexpr uint32_t SPLIT64_MIN_P = 4; // fewest particles per workgroup of the split step
 
 static inline size_t al256(size_t b) { return (b + 255) & ~size_t(255); }
@@ -50,12 +51,12 @@ Layout64 layout64_of(uint64_t N, int D)
     L.gpos = o;     o += al256(sizeof(double) * D);
     L.shift = o;    o += al256(sizeof(double) * D);
     // one slot per workgroup of a grid step (the split step's may hold only
-    // SPLIT64_MIN_P particles each), two per gang workgroup, six tagged
-    // words per staged-gang workgroup
-    const uint64_t nslots = std::max<uint64_t>(6 * (uint64_t)L.nblocks, (N + SPLIT64_MIN_P - 1) / SPLIT64_MIN_P);
+    // SPLIT64_MIN_P particles each), two per gang workgroup
+    const uint64_t nslots = std::max<uint64_t>(2 * (uint64_t)L.nblocks, (N + SPLIT64_MIN_P - 1) / SPLIT64_MIN_P);
     L.slot_ord = o; o += al256(sizeof(unsigned long long) * nslots);
     L.slot_idx = o; o += al256(sizeof(uint32_t) * nslots);
-    L.cand_pos = o; o += al256(sizeof(double) * 4 * L.nblocks * (size_t)D); // two parities; tagged words: two per double
+    L.cand_pos = o; o += al256(sizeof(double) * 2 * L.nblocks * (size_t)D); // two parities
+    L.gang_words = o; o += al256(sizeof(unsigned long long) * gang64_words(N, D));
     L.pf = o;       o += al256(sizeof(double) * L.Np);
     L.pend = o;     o += al256(L.Np);
     L.x = o;        o += al256(sizeof(double) * L.Np * (size_t)D);
@@ -75,6 +76,7 @@ Swarm64Args bind64(void *base, const Layout64 &L, uint64_t N, int D)
     a.slot_ord = reinterpret_cast<unsigned long long *>(b + L.slot_ord);
     a.slot_idx = reinterpret_cast<uint32_t *>(b + L.slot_idx);
     a.cand_pos = reinterpret_cast<double *>(b + L.cand_pos);
+    a.gang_words = L.pf > L.gang_words ? reinterpret_cast<unsigned long long *>(b + L.gang_words) : nullptr;
     a.pf = reinterpret_cast<double *>(b + L.pf);
     a.pend = reinterpret_cast<uint8_t *>(b + L.pend);
     a.x = reinterpret_cast<double *>(b + L.x);
@@ -84,85 +86,6 @@ Swarm64Args bind64(void *base, const Layout64 &L, uint64_t N, int D)
     a.Np = (uint32_t)L.Np;
     a.D = D;
     return a;
-}
-
-// Order bits of a binary64: unsigned order = numeric order, -0 = +0, NaN last.
-__device__ __forceinline__ unsigned long long ord64(double f)
-{
-    if (f != f) return ~0ull;
-    if (f == 0.0) f = 0.0;
-    const unsigned long long b = (unsigned long long)__double_as_longlong(f);
-    return (b & 0x8000000000000000ull) ? ~b : (b | 0x8000000000000000ull);
-}
-
-// Inverse of ord64 (for non-NaN values; -0 comes back as +0).
-__device__ __forceinline__ double ord64_value(unsigned long long o)
-{
-    const unsigned long long b = (o & 0x8000000000000000ull) ? (o & 0x7FFFFFFFFFFFFFFFull) : ~o;
-    return __longlong_as_double((long long)b);
-}
-
-__device__ __forceinline__ double clampd(double v, double lo, double hi)
-{
-    v = (v < lo) ? lo : v;
-    return (v > hi) ? hi : v;
-}
-
-// cos(pi y) after the exact reduction y = n + r.
-__device__ __forceinline__ double cospi64(double y)
-{
-    const double n = rint(y);
-    const double r = y - n;
-    const double c = cos(M_PI * r);
-    return fmod(n, 2.0) != 0.0 ? -c : c;
-}
-
-// The fitness functions in binary64, accumulated in dimension order.
-template <int FIT>
-struct Fitness64 {
-    double acc = 0.0, aux = 0.0;
-
-    __device__ __forceinline__ void add(double z, int d)
-    {
-        if constexpr (FIT == F_SPHERE) {
-            acc = acc + z * z;
-        } else if constexpr (FIT == F_RASTRIGIN) {
-            acc = acc + (z * z - 10.0 * cospi64(2.0 * z));
-        } else if constexpr (FIT == F_ROSENBROCK) {
-            if (d > 0) {
-                const double a = z - aux * aux;
-                const double b = 1.0 - aux;
-                acc = acc + (100.0 * a * a + b * b);
-            }
-            aux = z;
-        } else if constexpr (FIT == F_ACKLEY) {
-            acc = acc + z * z;
-            aux = aux + cospi64(2.0 * z);
-        } else {
-            acc = acc + (z * z * z - 0.8 * z * z - 1000.0 * z + 8000.0);
-        }
-    }
-
-    __device__ __forceinline__ double value(int D) const
-    {
-        if constexpr (FIT == F_RASTRIGIN) {
-            return 10.0 * D + acc;
-        } else if constexpr (FIT == F_ACKLEY) {
-            return 20.0 - 20.0 * exp(-0.2 * sqrt(acc / D)) + M_E - exp(aux / D);
-        } else if constexpr (FIT == F_CUBIC) {
-            return -acc; // Eq. 3, negated: the paper maximises it
-        } else {
-            return acc;
-        }
-    }
-};
-
-__device__ __forceinline__ void lexmin(unsigned long long &k, uint32_t &i, unsigned long long k2, uint32_t i2)
-{
-    if (k2 < k || (k2 == k && i2 < i)) {
-        k = k2;
-        i = i2;
-    }
 }
 
 // Workgroup lexicographic minimum of (k, i) over LANES lanes; the result is
@@ -201,30 +124,6 @@ __device__ void wg_lexmin(unsigned long long &k, uint32_t &i, unsigned long long
         i = s_i[0];
     }
     __syncthreads();
-}
-
-// Wavefront lexicographic minimum of the candidates (lanes with i != NO_IDX,
-// k != ~0) in every lane.  Beating the gbest is rare after the first
-// iterations, so a wavefront with no candidate or one takes no shuffles.
-__device__ __forceinline__ void wave_lexmin_sparse(unsigned long long &k, uint32_t &i)
-{
-    const unsigned long long m = __ballot(i != NO_IDX);
-    if (m == 0) {
-        k = ~0ull;
-        i = NO_IDX;
-    } else if ((m & (m - 1)) == 0) {
-        const int l = __builtin_ctzll(m);
-        const uint32_t lo = __builtin_amdgcn_readlane((uint32_t)k, l), hi = __builtin_amdgcn_readlane((uint32_t)(k >> 32), l);
-        k = ((unsigned long long)hi << 32) | lo;
-        i = __builtin_amdgcn_readlane(i, l);
-    } else {
-#pragma unroll
-        for (int off = 32; off >= 1; off >>= 1) {
-            const unsigned long long k2 = __shfl_xor(k, off, 64);
-            const uint32_t i2 = __shfl_xor(i, off, 64);
-            lexmin(k, i, k2, i2);
-        }
-    }
 }
 
 // Workgroup form of wave_lexmin_sparse: the wavefront minima meet in LDS
@@ -878,7 +777,6 @@ __global__ void __launch_bounds__(LANES) k_block_run64(Swarm64Args a, long long 
 // wall clock and sets an error bit if it gives up.
 // ---------------------------------------------------------------------------
 constexpr unsigned long long GANG64_WAIT_TICKS = 2000000000ull; // 20 s of the 100 MHz wall clock
-constexpr uint32_t GANG64S_MAX_G = 256;                          // workgroups of a staged gang at most
 
 template <int FIT>
 __global__ void __launch_bounds__(BLOCK64) k_gang64(Swarm64Args a, long long T, uint32_t per_wg)
@@ -978,169 +876,6 @@ __global__ void __launch_bounds__(BLOCK64) k_gang64(Swarm64Args a, long long T, 
     }
 }
 
-// The gang with each workgroup's slice of the swarm (x, v, p as rows of
-// per_wg doubles, pf) in LDS for the whole run, loaded once and stored back
-// at the end, so an iteration reads no state from device memory.  The
-// meeting uses no fences: every word a workgroup posts -- its key (order
-// bits in two words, index in one) and its candidate position (two words
-// per double) -- carries the iteration number in its high half and is
-// written and read with relaxed device-scope atomics, which are coherent
-// per word; a reader waits for each word it needs to carry the current
-// iteration.  (An agent-scope release and acquire write back and
-// invalidate the XCD's L2: 1.2-3 us of an iteration.)  Words of the other
-// parity cannot be overwritten early: a workgroup posts iteration t + 2
-// only after every workgroup has posted t + 1, after reading t.  The words
-// are cleared before each launch (a previous run's iteration numbers could
-// match).  Same arithmetic and choice of gbest as k_gang64, so the same
-// results.
-template <int FIT, bool ONE>
-__global__ void __launch_bounds__(BLOCK64) k_gang64s(Swarm64Args a, long long T, uint32_t per_wg)
-{
-    __shared__ unsigned long long s_k[BLOCK64 / 64];
-    __shared__ uint32_t s_i[BLOCK64 / 64];
-    __shared__ int s_fail;
-    __shared__ uint32_t s_word[3 * GANG64S_MAX_G]; // payloads of the tagged words read in a meeting
-    extern __shared__ double s_dyn64[]; // gbest position (D), shift (D), x, v, p (D x per_wg each), pf (per_wg)
-    Ctrl64 *c = a.ctrl;
-    const int D = ONE ? 1 : a.D;
-    const uint32_t G = gridDim.x, b = blockIdx.x;
-    const uint32_t i_lo = b * per_wg, n_loc = min(a.N, i_lo + per_wg) - i_lo;
-    const size_t Np = a.Np, rows = (size_t)D * per_wg;
-    double *s_g = s_dyn64, *s_shift = s_g + D, *sx = s_shift + D, *sv = sx + rows, *sp = sv + rows, *spf = sp + rows;
-    for (int d = threadIdx.x; d < D; d += BLOCK64) {
-        s_g[d] = a.gpos[d];
-        s_shift[d] = a.shift[d];
-    }
-    for (size_t e = threadIdx.x; e < rows; e += BLOCK64) {
-        const size_t d = e / per_wg, j = e % per_wg;
-        if (j < n_loc) {
-            const size_t g = d * Np + i_lo + j;
-            sx[e] = a.x[g];
-            sv[e] = a.v[g];
-            sp[e] = a.p[g];
-        }
-    }
-    for (uint32_t j = threadIdx.x; j < n_loc; j += BLOCK64) spf[j] = a.pf[i_lo + j];
-    unsigned long long gk = c->gord;
-    uint32_t gi = c->gidx;
-    long long giter = c->giter, t = c->t;
-    bool stop = c->stop != 0;
-    const double tol = c->tol, fstar = c->fstar;
-    double vlo = -a.vmax, vhi = a.vmax, xlo = a.lo, xhi = a.hi;
-    asm volatile("" : "+v"(vlo), "+v"(vhi), "+v"(xlo), "+v"(xhi));
-    if (threadIdx.x == 0) s_fail = 0;
-    __syncthreads();
-    for (long long it = 0; it < T && !stop; ++it) {
-        const uint32_t t1 = (uint32_t)(t + 1);
-        const int par = (int)(it & 1);
-        unsigned long long k = ~0ull;
-        uint32_t ki = NO_IDX;
-        for (uint32_t j = threadIdx.x; j < n_loc; j += BLOCK64)
-            staged_particle64<FIT>(a, D, per_wg, j, i_lo + j, t1, sx, sv, sp, spf, s_g, s_shift, vlo, vhi, xlo, xhi,
-                                   gk, gi, k, ki);
-        wg_lexmin_sparse<BLOCK64>(k, ki, s_k, s_i); // its barrier follows every lane's LDS stores
-        // post: the key (order bits in two words, index in one) and the
-        // candidate position (two words per double), each word tagged with t1
-        const unsigned long long tag = (unsigned long long)t1 << 32;
-        unsigned long long *kw = a.slot_ord + (size_t)par * G * 3, *pw =
-            reinterpret_cast<unsigned long long *>(a.cand_pos) + (size_t)par * G * 2 * D;
-        if (threadIdx.x < 3) {
-            const uint32_t pay = threadIdx.x == 0 ? (uint32_t)k : threadIdx.x == 1 ? (uint32_t)(k >> 32) : ki;
-            __hip_atomic_store(&kw[(size_t)b * 3 + threadIdx.x], tag | pay, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        } else if (threadIdx.x < 3 + 2 * (uint32_t)D) {
-            const uint32_t w = threadIdx.x - 3;
-            const double v = ki != NO_IDX ? sx[(size_t)(w >> 1) * per_wg + (ki - i_lo)] : 0.0;
-            const unsigned long long bits = (unsigned long long)__double_as_longlong(v);
-            const uint32_t pay = (w & 1) ? (uint32_t)(bits >> 32) : (uint32_t)bits;
-            __hip_atomic_store(&pw[(size_t)b * 2 * D + w], tag | pay, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        }
-        // every workgroup reads every key, each word once it carries t1
-        const unsigned long long w0 = wall_clock64();
-        for (uint32_t q = threadIdx.x; q < 3 * G; q += BLOCK64) {
-            unsigned long long v;
-            while (((v = __hip_atomic_load(&kw[q], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) >> 32) != t1) {
-                __builtin_amdgcn_s_sleep(1);
-                if (wall_clock64() - w0 > GANG64_WAIT_TICKS) {
-                    s_fail = 1;
-                    break;
-                }
-            }
-            s_word[q] = (uint32_t)v;
-        }
-        __syncthreads();
-        if (s_fail) { // uniform
-            if (threadIdx.x == 0) atomicOr(&c->err, 1u);
-            break;
-        }
-        unsigned long long rk = ~0ull;
-        uint32_t ri = NO_IDX;
-        for (uint32_t w = threadIdx.x; w < G; w += BLOCK64) {
-            const unsigned long long sk = ((unsigned long long)s_word[3 * w + 1] << 32) | s_word[3 * w];
-            const uint32_t si = s_word[3 * w + 2];
-            if (sk < rk || (sk == rk && si < ri)) {
-                rk = sk;
-                ri = si;
-            }
-        }
-        wg_lexmin(rk, ri, s_k, s_i); // ends with a barrier: s_word is free again
-        if (ri != NO_IDX) {
-            // the winner's position, from its workgroup's tagged words
-            const unsigned long long *src = pw + (size_t)(ri / per_wg) * 2 * D;
-            for (uint32_t w = threadIdx.x; w < 2 * (uint32_t)D; w += BLOCK64) {
-                unsigned long long v;
-                while (((v = __hip_atomic_load(&src[w], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) >> 32) != t1) {
-                    __builtin_amdgcn_s_sleep(1);
-                    if (wall_clock64() - w0 > GANG64_WAIT_TICKS) {
-                        s_fail = 1;
-                        break;
-                    }
-                }
-                s_word[w] = (uint32_t)v;
-            }
-            __syncthreads();
-            if (s_fail) { // uniform
-                if (threadIdx.x == 0) atomicOr(&c->err, 1u);
-                break;
-            }
-            for (int d = threadIdx.x; d < D; d += BLOCK64)
-                s_g[d] = __longlong_as_double((long long)(((unsigned long long)s_word[2 * d + 1] << 32) | s_word[2 * d]));
-            gk = rk;
-            gi = ri;
-            giter = t1;
-        }
-        t = t1;
-        // every workgroup holds the same key, so all take the same decision
-        stop = tol > 0.0 && fabs(ord64_value(gk) - fstar) < tol;
-        __syncthreads();
-    }
-    for (size_t e = threadIdx.x; e < rows; e += BLOCK64) {
-        const size_t d = e / per_wg, j = e % per_wg;
-        if (j < n_loc) {
-            const size_t g = d * Np + i_lo + j;
-            a.x[g] = sx[e];
-            a.v[g] = sv[e];
-            a.p[g] = sp[e];
-        }
-    }
-    for (uint32_t j = threadIdx.x; j < n_loc; j += BLOCK64) a.pf[i_lo + j] = spf[j];
-    if (b == 0) {
-        for (int d = threadIdx.x; d < D; d += BLOCK64) a.gpos[d] = s_g[d];
-        if (threadIdx.x == 0) {
-            c->gord = gk;
-            c->gidx = gi;
-            c->giter = giter;
-            c->t = t;
-            c->stop = stop ? 1u : 0u;
-        }
-    }
-}
-
-// Zeroes n words (the staged gang's tagged slots before a launch).
-__global__ void k_zero64(unsigned long long *w, size_t n)
-{
-    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) w[i] = 0;
-}
-
 // Clears the control block (a kernel, not a memset: the call may be
 // captured into a graph).
 __global__ void k_reset64(Swarm64Args a)
@@ -1160,7 +895,24 @@ __global__ void k_arm64(Swarm64Args a, double tol, double fstar)
     Ctrl64 *c = a.ctrl;
     c->tol = tol;
     c->fstar = fstar;
+    c->gang_here = 0;
+    c->gang_state = 0;
     c->stop = (tol > 0.0 && fabs(a.pf[c->gidx] - fstar) < tol) ? 1u : 0u;
+}
+
+// The resident gang's rendezvous fields before each of its launches after
+// the first (k_arm64 clears them too).
+__global__ void k_gang_arm64(Swarm64Args a)
+{
+    if (threadIdx.x != 0) return;
+    a.ctrl->gang_here = 0;
+    a.ctrl->gang_state = 0;
+}
+
+hipError_t launch64_gang_arm(const Swarm64Args &a, hipStream_t stream)
+{
+    hipLaunchKernelGGL(k_gang_arm64, dim3(1), dim3(64), 0, stream, a);
+    return hipGetLastError();
 }
 
 static inline dim3 grid64(const Swarm64Args &a) { return dim3((a.N + BLOCK64 - 1) / BLOCK64); }
@@ -1351,61 +1103,15 @@ static int gang_ppl(uint64_t N)
     return N <= 8192 ? 2 : N <= 65536 ? 4 : 8;
 }
 
-// The gang with its slices in LDS (k_gang64s) where a slice fits and the
-// workgroups are co-resident; else k_gang64 at gang_ppl's count
-// (PSO64_GANG_STAGED=0 in the environment: always k_gang64, for tests).
+// The gang at gang_ppl's count, where its workgroups are co-resident.
 template <int FIT>
-static hipError_t gang64_f(const Swarm64Args &a, long long T, hipStream_t s, bool *launched, bool staged_only)
+static hipError_t gang64_f(const Swarm64Args &a, long long T, hipStream_t s, bool *launched)
 {
-    const int ppl0 = gang_ppl(a.N);
-    // staged: the fence-free meeting is cheap, so as many workgroups as the
-    // tagged words allow (Cubic 1D, us per iteration at 1/2/4/8 particles
-    // per lane: N = 4096: 3.0/3.1/3.5/4.6; 16384: 3.6/3.8/4.0/5.0; 65536:
-    // 4.3/4.3/4.7/5.7; 131072: -/4.8/5.0/5.9)
-    const char *penv = getenv("PSO64_GANG_PPL");
-    const int ppl_s = penv ? ppl0
-                           : (int)std::max<uint64_t>(1, ((uint64_t)a.N + (uint64_t)BLOCK64 * GANG64S_MAX_G - 1) /
-                                                             ((uint64_t)BLOCK64 * GANG64S_MAX_G));
     int per_cu = 0, dev = 0, cus = 0;
     hipError_t e = hipGetDevice(&dev);
     if (e != hipSuccess) return e;
     if ((e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev)) != hipSuccess) return e;
-    const char *env = getenv("PSO64_GANG_STAGED");
-    const bool one = a.D == 1;
-    for (int ppl = ppl_s; !(env && !strcmp(env, "0")) && lds64_max() > 0 && ppl >= std::max(1, ppl_s / 2); ppl /= 2) {
-        const uint64_t per_wg = BLOCK64 * (uint64_t)ppl; // particles per workgroup
-        const uint64_t G = ((uint64_t)a.N + per_wg - 1) / per_wg;
-        const size_t lds_s = sizeof(double) * (2 * (size_t)a.D + (3 * (size_t)a.D + 1) * per_wg);
-        const size_t lds_static = sizeof(uint32_t) * 3 * GANG64S_MAX_G + 1024; // the kernel's own arrays, with room
-        if (lds_s + lds_static > (size_t)lds64_max()) continue;
-        const void *f = one ? reinterpret_cast<const void *>(k_gang64s<FIT, true>)
-                            : reinterpret_cast<const void *>(k_gang64s<FIT, false>);
-        // the most any swarm may ask for, so concurrent callers never lower it
-        if ((e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                     lds64_max() - (int)lds_static)) != hipSuccess)
-            return e;
-        e = one ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_gang64s<FIT, true>, BLOCK64, lds_s)
-                : hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_gang64s<FIT, false>, BLOCK64, lds_s);
-        if (e != hipSuccess) return e;
-        if (G > (uint64_t)std::max(1, per_cu * cus * 3 / 4) || G > GANG64S_MAX_G) continue; // co-resident with margin
-        // the tagged words of both parities: keys in slot_ord, positions in cand_pos
-        hipLaunchKernelGGL(k_zero64, dim3(4), dim3(256), 0, s, a.slot_ord, (size_t)6 * G);
-        hipLaunchKernelGGL(k_zero64, dim3(4), dim3(256), 0, s, reinterpret_cast<unsigned long long *>(a.cand_pos),
-                           (size_t)4 * G * a.D);
-        if (one)
-            hipLaunchKernelGGL((k_gang64s<FIT, true>), dim3((unsigned)G), dim3(BLOCK64), lds_s, s, a, T,
-                               (uint32_t)per_wg);
-        else
-            hipLaunchKernelGGL((k_gang64s<FIT, false>), dim3((unsigned)G), dim3(BLOCK64), lds_s, s, a, T,
-                               (uint32_t)per_wg);
-        *launched = true;
-        return hipGetLastError();
-    }
-    if (staged_only) {
-        *launched = false;
-        return hipSuccess;
-    }
-    const uint64_t per_wg = BLOCK64 * (uint64_t)ppl0;
+    const uint64_t per_wg = BLOCK64 * (uint64_t)gang_ppl(a.N);
     const uint64_t G = ((uint64_t)a.N + per_wg - 1) / per_wg;
     const size_t lds = 2 * sizeof(double) * a.D;
     if ((e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_gang64<FIT>, BLOCK64, lds)) != hipSuccess) return e;
@@ -1419,15 +1125,14 @@ static hipError_t gang64_f(const Swarm64Args &a, long long T, hipStream_t s, boo
     return hipGetLastError();
 }
 
-hipError_t launch64_gang(int fitness, const Swarm64Args &a, long long T, hipStream_t stream, bool *launched,
-                         bool staged_only)
+hipError_t launch64_gang(int fitness, const Swarm64Args &a, long long T, hipStream_t stream, bool *launched)
 {
     switch (fitness) {
-    case F_SPHERE: return gang64_f<F_SPHERE>(a, T, stream, launched, staged_only);
-    case F_RASTRIGIN: return gang64_f<F_RASTRIGIN>(a, T, stream, launched, staged_only);
-    case F_ROSENBROCK: return gang64_f<F_ROSENBROCK>(a, T, stream, launched, staged_only);
-    case F_ACKLEY: return gang64_f<F_ACKLEY>(a, T, stream, launched, staged_only);
-    case F_CUBIC: return gang64_f<F_CUBIC>(a, T, stream, launched, staged_only);
+    case F_SPHERE: return gang64_f<F_SPHERE>(a, T, stream, launched);
+    case F_RASTRIGIN: return gang64_f<F_RASTRIGIN>(a, T, stream, launched);
+    case F_ROSENBROCK: return gang64_f<F_ROSENBROCK>(a, T, stream, launched);
+    case F_ACKLEY: return gang64_f<F_ACKLEY>(a, T, stream, launched);
+    case F_CUBIC: return gang64_f<F_CUBIC>(a, T, stream, launched);
     default: return hipErrorInvalidValue;
     }
 }
@@ -1493,30 +1198,21 @@ namespace {
         if (e_ != hipSuccess) return pso_internal_fail(PSO_EDEVICE, "%s: %s", #expr, hipGetErrorString(e_));      \
     } while (0)
 
-// Paths of pso64_run (Cubic, us per iteration).  A swarm that the split grid
-// step takes (D >= 32, N <= 32768) runs one grid launch per iteration: its
-// lanes share each particle's dimensions, where one workgroup gives a lane a
-// whole particle (grid / one workgroup: N = 32, D = 120: 8.8 / 31.1; 64,
-// 100: 8.8 / 24.5; 128, 40: 8.4 / 10.9; 192, 32: 8.6 / 8.9).  Else a swarm
-// whose state fits the LDS of one workgroup (x, v, p and pf: about 6 700
-// particle-dimensions) runs there in one launch (256, 24: 7.1 against 12.7
-// for the grid; 512, 8: 3.3 against 4.6 for the gang) unless the gang takes
-// it (D <= GANG64_MAX_D and N >= GANG64_MIN_N; one workgroup / gang at D =
-// 1: N = 3000: 2.55 / 2.82; 4096: 3.21 / 2.87; 5000: 3.86 / 3.03); else for
-// D <= GANG64_MAX_D the persistent gang (N = 16384: 3.4; 131072: 4.7;
-// D = 8, N = 16384: 5.7); else one grid launch per iteration (at D = 120
-// the unstaged gang and the grid were within 2 % at N = 8192).  PSO64_PATH
-// (block, gang, grid) overrides the choice (tests of every path); with
-// PSO64_BLOCK_STAGED=0 the one-workgroup run keeps the state in device
-// memory and takes up to BLOCK64_MAX_ND.
+// Paths of pso64_run.  The resident gang takes every swarm it accepts and
+// holds (pso_gang64.hip).  Of the others (Cubic, us per iteration): a swarm
+// that the split grid step takes (D >= 32, N <= 32768) runs one grid launch
+// per iteration (grid / one workgroup: N = 32, D = 120: 8.8 / 31.1; 192, 32:
+// 8.6 / 8.9); else a swarm whose state fits the LDS of one workgroup (x, v, p
+// and pf: about 6 700 particle-dimensions) runs there in one launch; else for
+// D <= GANG64_MAX_D the persistent gang over device memory, where its
+// workgroups are co-resident; else one grid launch per iteration (at D = 120
+// the gang and the grid were within 2 % at N = 8192).  PSO64_PATH (block, gang,
+// grid) overrides the choice (tests of every path; gang with
+// PSO64_GANG_STAGED=0: the gang over device memory); with
+// PSO64_BLOCK_STAGED=0 the one-workgroup run keeps the state in device memory
+// and takes up to BLOCK64_MAX_ND.
 constexpr uint64_t BLOCK64_MAX_ND = 2048;
 constexpr int GANG64_MAX_D = 8;
-// with its slices in LDS the gang also beats the grid up to D = 31 (staged
-// gang / grid: N = 4096, D = 12: 6.1 / 9.3; 16384, 16: 7.9 / 14.0; 16384,
-// 24: 9.7 / 17.5); where the slices do not fit or co-reside (N = 65536, D =
-// 16: 29.6 in device memory against 17.2) the grid runs
-constexpr int GANG64_STAGED_MAX_D = 32;
-constexpr uint32_t GANG64_MIN_N = 4096; // from here the gang beats one workgroup (D = 1, N = 4096: 2.9 / 3.2 us)
 
 void free64(pso_swarm64 *s)
 {
@@ -1531,6 +1227,44 @@ int reinit64(pso_swarm64 *s)
 {
     HIP64_TRY(pso::launch64_reset(s->a, s->stream));
     HIP64_TRY(pso::launch64_init(s->fitness, s->a, s->stream));
+    return PSO_OK;
+}
+
+// Runs the swarm's next iterations as a resident gang where that suits it,
+// and takes what it ran off *left; *absent: its parts were not resident
+// together, so no other gang is tried either.  A launch is kept to about 50 ms
+// (an iteration takes at most about 1.5 us and 10 us per million
+// particle-dimensions) so that other work on the device waits no longer.
+int gang_run64(pso_swarm64 *s, const char *path, int64_t *left, bool *absent)
+{
+    const char *staged = getenv("PSO64_GANG_STAGED");
+    if (path && (strcmp(path, "gang") || (staged && !strcmp(staged, "0")))) return PSO_OK;
+    // a grid step or one-workgroup form forced from the environment is meant
+    if (!path)
+        for (const char *name : {"PSO64_WIDE", "PSO64_SPLIT", "PSO64_BLOCK_STAGED"})
+            if (getenv(name)) return PSO_OK;
+    pso::Gang64Shape sh;
+    if (!pso::gang64_accepts(s->fitness, s->a) || !pso::gang64_shape(s->fitness, s->a, *left, &sh)) return PSO_OK;
+    const int64_t most =
+        std::max<int64_t>(64, std::min<int64_t>(pso::GANG_MAX_T, int64_t(50000.0 / (1.5 + 1e-5 * double(s->N) * s->D))));
+    for (bool first = true; *left > 0; first = false) {
+        const int64_t T = std::min(*left, most);
+        if (!first) HIP64_TRY(pso::launch64_gang_arm(s->a, s->stream));
+        HIP64_TRY(pso::launch_gang64(s->fitness, s->a, sh, (uint32_t)T, s->stream));
+        if (T == *left && sh.G == 1) {
+            *left = 0; // nothing to learn from the control block
+            break;
+        }
+        pso::Ctrl64 c{};
+        HIP64_TRY(hipStreamSynchronize(s->stream));
+        HIP64_TRY(hipMemcpy(&c, s->a.ctrl, sizeof c, hipMemcpyDeviceToHost));
+        if (c.err) return pso_internal_fail(PSO_EDEVICE, "a gang wait gave up (device error bits 0x%x)", c.err);
+        if (c.gang_state == pso::GANG_ABSENT) {
+            *absent = true;
+            break;
+        }
+        *left = c.stop ? 0 : *left - T;
+    }
     return PSO_OK;
 }
 
@@ -1647,14 +1381,19 @@ int pso64_run(pso_swarm64 *s, int64_t max_iter, double tol, double f_star, doubl
         HIP64_TRY(pso::launch64_arm(s->a, tol, f_star, s->stream));
         const uint64_t nd = s->N * (uint64_t)s->D;
         const char *path = getenv("PSO64_PATH"); // tests of every path: block, gang, grid
-        bool done_gang = false;
-        const bool block = path ? !strcmp(path, "block")
-                                : !pso::step64_split(s->fitness, s->a) &&
-                                      !(s->D <= GANG64_MAX_D && s->N >= GANG64_MIN_N) &&
-                                      (pso::block64_staged_fits(s->a) || nd <= BLOCK64_MAX_ND);
-        // 8 < D < 32: the gang only with its slices in LDS, else the grid
-        const bool gang_staged_only = !path && s->D > GANG64_MAX_D;
-        const bool gang = !block && (path ? !strcmp(path, "gang") : s->D < GANG64_STAGED_MAX_D);
+        // the resident gang runs what it can; max_iter keeps what is left for
+        // the other paths (all of it where its parts were not resident)
+        bool absent = false;
+        if (max_iter > 0) {
+            int rc = gang_run64(s, path, &max_iter, &absent);
+            if (rc) return rc;
+        }
+        bool done_gang = max_iter == 0;
+        const bool block = !done_gang && (path ? !strcmp(path, "block")
+                                               : !pso::step64_split(s->fitness, s->a) &&
+                                                     (pso::block64_staged_fits(s->a) || nd <= BLOCK64_MAX_ND));
+        const bool gang = !done_gang && !block && !absent &&
+                          (path ? !strcmp(path, "gang") : s->D <= GANG64_MAX_D);
         // those paths write each pbest position at once: complete the
         // pending ones a wide grid step left
         if (block || gang) HIP64_TRY(pso::launch64_flush(s->a, s->stream));
@@ -1663,7 +1402,7 @@ int pso64_run(pso_swarm64 *s, int64_t max_iter, double tol, double f_star, doubl
             done_gang = true;
         } else if (gang) {
             HIP64_TRY(hipMemsetAsync(&s->a.ctrl->gang_arrive, 0, sizeof(unsigned long long), s->stream));
-            HIP64_TRY(pso::launch64_gang(s->fitness, s->a, max_iter, s->stream, &done_gang, gang_staged_only));
+            HIP64_TRY(pso::launch64_gang(s->fitness, s->a, max_iter, s->stream, &done_gang));
         }
         if (!done_gang) {
             // chunks of launches; every launch returns at once after the stop rule holds

@@ -20,7 +20,8 @@ struct alignas(256) Ctrl64 {
     uint32_t err;            // a bounded wait of the gang kernel gave up
     double tol, fstar;       // stop rule |gbest - fstar| < tol (tol <= 0: off)
     unsigned long long gang_arrive; // gang kernel: workgroup arrivals (monotonic within a launch)
-    unsigned char pad2[184];
+    uint32_t gang_here, gang_state; // resident gang: parts at a launch's rendezvous, its outcome (GANG_GO, GANG_ABSENT)
+    unsigned char pad2[176];
 };
 static_assert(sizeof(Ctrl64) == 256, "Ctrl64 layout");
 
@@ -28,9 +29,10 @@ struct Swarm64Args {
     double *x, *v, *p, *pf;        // D*Np, D*Np, D*Np, Np; element (d, i) at d*Np + i
     double *gpos;                  // D
     const double *shift;           // D
-    unsigned long long *slot_ord;  // one per grid workgroup (gang: two per workgroup by parity; staged gang: six tagged words)
+    unsigned long long *slot_ord;  // one per grid workgroup (gang: two per workgroup by parity)
     uint32_t *slot_idx;            // as slot_ord
-    double *cand_pos;              // gang: [parity][workgroup][D] candidate positions (staged gang: tagged words)
+    double *cand_pos;              // gang: [parity][workgroup][D] candidate positions
+    unsigned long long *gang_words; // resident gang: the parts' meeting words (null: none)
     uint8_t *pend;                 // Np: 1 = pbest position of i is x, not yet in p (wide grid step)
     Ctrl64 *ctrl;
     uint32_t N, Np;
@@ -40,7 +42,7 @@ struct Swarm64Args {
 };
 
 struct Layout64 {
-    size_t ctrl, gpos, shift, slot_ord, slot_idx, cand_pos, pf, pend, x, v, p, total;
+    size_t ctrl, gpos, shift, slot_ord, slot_idx, cand_pos, gang_words, pf, pend, x, v, p, total;
     uint64_t Np;
     uint32_t nblocks;
 };
@@ -69,8 +71,28 @@ hipError_t launch64_eval(int fitness, const Swarm64Args &a, const double *pts, u
 // once per iteration (bit-identical to T grid steps); ctrl->gang_arrive must
 // be zero.  *launched = false if the swarm needs more workgroups than can be
 // co-resident (nothing is enqueued then).
-// staged_only: launch only the gang with its slices in LDS (*launched false otherwise).
-hipError_t launch64_gang(int fitness, const Swarm64Args &a, long long T, hipStream_t stream, bool *launched,
-                         bool staged_only = false);
+hipError_t launch64_gang(int fitness, const Swarm64Args &a, long long T, hipStream_t stream, bool *launched);
+
+// The resident gang (pso_gang64.hip): a whole run by co-resident workgroups
+// that hold the swarm in registers; see pso_gang.hpp for the binary32 form.
+struct Gang64Args {
+    uint32_t T;                // iterations of the launch (at most GANG_MAX_T)
+    uint32_t P, L;             // particles per part, lanes per particle
+    float block_ratio;         // a meeting's time over an iteration's
+    double c1s, c2s;           // c1 2^-24, c2 2^-24 (exact)
+    unsigned long long *words; // the parts' meeting words
+};
+struct Gang64Shape {
+    const void *fn;
+    int C;
+    uint32_t P, L, G, lanes;
+    size_t lds;
+};
+constexpr int GANG64_MAX_D_ALL = 512; // no instantiation holds more dimensions
+bool gang64_accepts(int fitness, const Swarm64Args &a);
+bool gang64_shape(int fitness, const Swarm64Args &a, int64_t T, Gang64Shape *out);
+size_t gang64_words(uint64_t N, int D); // 64-bit words reserved in the swarm's memory
+hipError_t launch64_gang_arm(const Swarm64Args &a, hipStream_t stream);
+hipError_t launch_gang64(int fitness, const Swarm64Args &a, const Gang64Shape &s, uint32_t T, hipStream_t stream);
 
 } // namespace pso

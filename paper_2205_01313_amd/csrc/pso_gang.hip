@@ -38,9 +38,12 @@
 // its first candidate.  The parts agree on the earliest iteration j that has
 // one (the least word); whoever ran past j restores the block's start from a
 // copy in registers and repeats j iterations.  What is committed is exactly
-// the synchronous method's trajectory.  K doubles after a block without a
-// change, and falls to j after one, so a swarm whose gbest changes every
-// iteration meets every iteration (K = 1: no copy, nothing repeated).
+// the synchronous method's trajectory.  A block costs a meeting M and, when the
+// gbest changes in it, about K iterations I run in vain or again; with a
+// change every m iterations that is least at K = sqrt(m M / I) (next_block: m
+// a running mean, M / I from the shape, block_ratio).  A swarm whose gbest
+// changes every iteration meets every iteration (K = 1: no copy, nothing
+// repeated).
 //
 // All parts must be resident together.  They meet once before they touch any
 // state; if they are not all there within RENDEZVOUS_TICKS (another kernel
@@ -57,11 +60,6 @@
 
 namespace pso {
 
-constexpr unsigned long long GANG_TICKS = 2000000000ull;   // 20 s of the 100 MHz wall clock: a part is lost
-constexpr unsigned long long RENDEZVOUS_TICKS = 200000ull; // 2 ms: the parts are not resident together
-constexpr uint32_t GANG_PARTS_MAX = 256;                   // one byte of the meeting's minimum
-constexpr int SPEC_MAX_K = 64;                             // iterations of a block at most (fits the word's 8 bits)
-constexpr int KEY_STRIDE = 8;                              // key words one per 64-byte line
 constexpr unsigned long long NO_COMB = ~0ull;
 
 // cos(2 pi z) for |2 z| < 2^22: cospi_f32's operations without the cases of
@@ -115,12 +113,6 @@ template <int C>
 struct OwnHalf { // of the next iteration: (w v) + ((c1 r1)(p - x)) and c2 r2
     float own[C], soc[C];
 };
-
-// Dimensions are taken in groups of four (all of C < 4): a group is skipped
-// whole past D, and otherwise computed whole -- two independent Philox draws
-// in straight-line code; dimensions of it past D hold values that nothing
-// reads.
-constexpr int group_of(int C) { return C < 4 ? C : 4; }
 
 // c1 r1 with r1 = u 2^-24, u an integer below 2^24, is one rounding of the
 // product c1 u 2^-24; with c1 2^-24 exact (gang_accepts) so is (c1 2^-24) u.
@@ -368,7 +360,7 @@ __global__ void __launch_bounds__(MAXT) k_gang_resident(SwarmArgs a, GangArgs ga
                 // a batch of terms is loaded before they are added, so the sum
                 // waits on LDS once a batch; terms past D are loaded (their
                 // place exists) but not added
-                constexpr int MOST = 16 / W; // terms of a batch
+                constexpr int MOST = (MAXT <= 512 ? 32 : 16) / W; // terms of a batch
                 constexpr int BS = C < MOST ? C : MOST, NB = MOST / BS; // of a chunk, chunks
                 for (int kk = 1; kk < L; kk += NB) {
                     const float *r = s_t + ((uint32_t)(kk - 1) * P + j) * CW;
@@ -435,6 +427,7 @@ __global__ void __launch_bounds__(MAXT) k_gang_resident(SwarmArgs a, GangArgs ga
 
     long long done = 0;
     int K = 1;
+    float mean = 1.0f, since = 0.0f; // iterations between gbest changes, and since the last
     uint32_t seq = 0;
     stop = stop || (tol > 0.0f && __builtin_fabsf(key_fitness(gkey) - fstar) < tol);
     while (done < (long long)ga.T && !stop) {
@@ -611,7 +604,7 @@ __global__ void __launch_bounds__(MAXT) k_gang_resident(SwarmArgs a, GangArgs ga
             s_gn = s_old;
         }
         done += nc;
-        K = changed ? min(nc, SPEC_MAX_K) : min(2 * K, SPEC_MAX_K);
+        K = SPEC ? next_block(changed, nc, ga.block_ratio, mean, since) : 1;
         stop = tol > 0.0f && __builtin_fabsf(key_fitness(gkey) - fstar) < tol;
     }
 
@@ -725,6 +718,31 @@ static const GangKernel *gang_kernels(int fitness, int *n)
     }
 }
 
+// Chosen by measurement (us per iteration of the first 200 and of 1000 at
+// ratios 0.2 / 1 / 4 / 16): Sphere D = 2, N = 1024 1.86 / 1.64 / 1.48 / 1.65
+// and 0.83 / 0.69 / 0.62 / 0.64; Sphere D = 10, N = 5000 (lanes share
+// particles) 2.89 / 2.92 / 3.36 / 4.67 and 1.58 / 1.43 / 1.47 / 1.74; Cubic D =
+// 1, N = 16384 1.10 / 0.77 / 0.65 / 0.59.  One part whose lanes share
+// particles stops as a whole at its first candidate, so nothing is repeated
+// and blocks are as long as they may be.
+float block_ratio(int C, uint32_t L, uint32_t lanes, uint32_t G, float weight)
+{
+    if (G == 1 && L > 1) return 1e6f;
+    const float meeting = G > 1 ? 1.5f + (float)G / 256.0f : 0.7f;
+    const float iteration = 0.15f + 0.1f * weight * (float)C * std::max(1.0f, (float)lanes / 512.0f) + (L > 1 ? 1.2f : 0.0f);
+    return meeting / iteration;
+}
+
+bool gang_device(int *cus, int *lds)
+{
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
+        hipDeviceGetAttribute(lds, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) != hipSuccess)
+        return false;
+    return true;
+}
+
 static size_t gang_lds(int fitness, int D, const GangKernel &kn, uint32_t P, uint32_t L)
 {
     const size_t lanes = ((size_t)P * L + 63) / 64 * 64;
@@ -737,16 +755,6 @@ static size_t gang_lds(int fitness, int D, const GangKernel &kn, uint32_t P, uin
     return sizeof(float) * f;
 }
 
-static int gang_device(int *cus, int *lds)
-{
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess ||
-        hipDeviceGetAttribute(cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-        hipDeviceGetAttribute(lds, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) != hipSuccess)
-        return 0;
-    return 1;
-}
-
 // One shape's kernel, lanes and LDS, or false if no instantiation holds it.
 static bool gang_layout(int fitness, const SwarmArgs &a, int C, uint32_t P, GangShape *out)
 {
@@ -756,7 +764,7 @@ static bool gang_layout(int fitness, const SwarmArgs &a, int C, uint32_t P, Gang
     const uint32_t L = ((uint32_t)a.D + C - 1) / C;
     const uint64_t lanes = ((uint64_t)P * L + 63) / 64 * 64, G = ((uint64_t)a.N + P - 1) / P;
     if (G > GANG_PARTS_MAX || G > (uint64_t)cus) return false;
-    if (P % 64 != 0 && P != 16 && P != 32) return false;
+    if (P < 16) return false;
     for (int q = 0; q < nk; ++q) {
         const GangKernel &kn = tab[q];
         if (kn.C != C || kn.multi != (L > 1) || (kn.tail && L != 2) || lanes > (uint64_t)kn.max_lanes) continue;
@@ -776,10 +784,10 @@ static bool gang_layout(int fitness, const SwarmArgs &a, int C, uint32_t P, Gang
 // the gbest changed).  Measured on Rastrigin over N = 32 .. 262144 and D = 1
 // .. 300 (the other functions choose alike), us per iteration of the shape
 // taken / the best of the others / the step launches or the one-workgroup run:
-//   one part (no meeting) up to N = 512 and N D = 4096, in up to 768 lanes:
-//     N = 32: D = 16 1.63 / 2.3 / 1.56, D = 64 2.75 / 3.2 / 2.76; N = 128:
-//     D = 8 1.47 / 2.4 / 1.63, D = 24 2.55 / 3.5 / 2.62; beyond, several:
-//     N = 300: D = 16 3.2 / 3.6 / 3.62; N = 200: D = 50 4.3 / 6.9 / 6.98
+//   one part (no meeting; one_part) while its lanes hold the swarm: N = 40, D =
+//     20 1.8 / 2.1 / 2.1; 100, 12 1.85 / 2.6 / 2.24; 257, 5 1.92 / 2.2 / 2.2;
+//     624, 2 1.66 / 1.94 / 1.66 (60 iterations; 0.89 / 0.81 / 1.26 of 300);
+//     below N = 32 with D > 24 the one-workgroup run is 6 % faster
 //   D <= 2: 256 particles of a part, one lane each (C = 1 for D = 1): N =
 //     16384, D = 2 1.05 / 1.08 / 6.27
 //   D <= 4: pairs of lanes with few particles each, 32 of a part, below N =
@@ -797,7 +805,7 @@ static bool gang_layout(int fitness, const SwarmArgs &a, int C, uint32_t P, Gang
 //   larger chunks where smaller ones need more lanes than a part has: N =
 //     65536: D = 64 C = 16 10.1 / 15.1 (C = 64) / 23.3; D = 128 C = 64 19.9 /
 //     39.2; N = 262144: D = 16 8.3 / 25.2, D = 30 C = 32 16.2 / 37.9
-bool gang_shape(int fitness, const SwarmArgs &a, GangShape *out)
+bool gang_shape(int fitness, const SwarmArgs &a, int64_t T, GangShape *out)
 {
     if (const char *env = getenv("PSO_GANG_SHAPE")) { // "C,P": forced (tests, measurements)
         int c = 0, p = 0;
@@ -806,12 +814,9 @@ bool gang_shape(int fitness, const SwarmArgs &a, GangShape *out)
     }
     const int D = a.D;
     const uint32_t N = a.N;
-    if (N <= 512 && (uint64_t)N * D <= 4096) {
-        const uint32_t P = N <= 32 && D > 2 ? 32 : (N + 63) / 64 * 64;
-        for (int c = D == 1 ? 1 : 2; c <= 8; c *= 2)
-            if (P * ((uint32_t)(D + c - 1) / c) <= (D <= 4 ? 1024u : 768u) && gang_layout(fitness, a, c, P, out))
-                return true;
-    }
+    if (N < 32 && D > 24 && D <= 110) return false;
+    if (one_part(N, D, T, 256, [&](int c, uint32_t P) { return gang_layout(fitness, a, c, P, out); }))
+        return true;
     int c = D == 1 ? 1 : 2;
     uint32_t pmin = 256;
     if (D > 64) c = 8, pmin = 16;
@@ -857,6 +862,7 @@ hipError_t launch_gang(const SwarmArgs &a, const GangShape &s, uint32_t T, unsig
     ga.c1s = std::ldexp(a.c1, -24);
     ga.c2s = std::ldexp(a.c2, -24);
     ga.words = words;
+    ga.block_ratio = block_ratio(s.C, s.L, s.lanes, s.G, 1.0f);
     void *params[] = {&args, &ga};
     return hipLaunchKernel(s.fn, dim3(s.G), dim3(s.lanes), params, s.lds, stream);
 }

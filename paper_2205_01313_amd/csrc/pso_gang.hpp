@@ -2,6 +2,8 @@
 // co-resident workgroups that hold it in registers (pso_gang.hip).
 #pragma once
 
+#include <algorithm>
+
 #include "pso_kernels.hpp"
 
 namespace pso {
@@ -10,9 +12,41 @@ namespace pso {
 constexpr unsigned int GANG_GO = 1u;     // all parts resident: the launch ran
 constexpr unsigned int GANG_ABSENT = 2u; // not all resident in time: nothing was touched
 
+constexpr unsigned long long GANG_TICKS = 2000000000ull;   // 20 s of the 100 MHz wall clock: a part is lost
+constexpr unsigned long long RENDEZVOUS_TICKS = 200000ull; // 2 ms: the parts are not resident together
+constexpr uint32_t GANG_PARTS_MAX = 256;                   // one byte of the meeting's minimum
+constexpr int SPEC_MAX_K = 64;                             // iterations of a block at most (fits the word's 8 bits)
+constexpr int KEY_STRIDE = 8;                              // key words one per 64-byte line
+
+// Dimensions are taken in groups of four (all of C < 4): a group is skipped
+// whole past D, and otherwise computed whole -- two independent Philox draws
+// in straight-line code; dimensions of it past D hold values that nothing
+// reads.
+constexpr int group_of(int C) { return C < 4 ? C : 4; }
+
+// Iterations of the next block, after one that committed nc iterations and
+// ended with a change of the gbest or without: sqrt(mean * ratio), the mean
+// number of iterations between changes halved towards each new one and never
+// below the iterations since the last.  The same in every part.
+__device__ __forceinline__ int next_block(bool changed, int nc, float ratio, float &mean, float &since)
+{
+    since += (float)nc;
+    if (changed) {
+        mean = 0.5f * (mean + since);
+        since = 0.0f;
+    } else {
+        mean = __builtin_fmaxf(mean, since);
+    }
+    const int k = (int)__builtin_sqrtf(mean * ratio);
+    return k < 1 ? 1 : (k > SPEC_MAX_K ? SPEC_MAX_K : k);
+}
+// M / I of a shape (weight: an iteration's work against binary32 Sphere's).
+float block_ratio(int C, uint32_t L, uint32_t lanes, uint32_t G, float weight);
+
 struct GangArgs {
     uint32_t T;                // iterations of the launch (at most GANG_MAX_T)
     uint32_t P, L;             // particles per part, lanes per particle
+    float block_ratio;         // a meeting's time over an iteration's
     float c1s, c2s;            // c1 2^-24, c2 2^-24 (exact)
     unsigned long long *words; // the parts' meeting words
 };
@@ -31,10 +65,33 @@ struct GangShape {
 // ranges its shorter instruction sequences are exact for; shift_max: largest
 // magnitude of the shift vector; state_set: pso_set_state was called).
 bool gang_accepts(int fitness, const SwarmArgs &a, float shift_max, bool state_set);
-// The swarm's shape, or false if none holds it.
-bool gang_shape(int fitness, const SwarmArgs &a, GangShape *out);
+// The swarm's shape for a run of T iterations, or false if none holds it.
+bool gang_shape(int fitness, const SwarmArgs &a, int64_t T, GangShape *out);
 // 64-bit device words of the meeting.
 size_t gang_words(uint32_t parts, int D);
+// A swarm small enough for one part: layout(C, P) with its particles packed
+// (whole wavefronts where a lane holds a particle) and the smallest chunk that
+// fits, from C = 4 on for D > 12, whose fold is shorter that way.  A brief run
+// spends its iterations where the gbest still changes often and every change
+// is a meeting, so it stays in one part longer (Sphere D = 2, N = 818, one part
+// / four: 1.81 / 2.17 us per iteration of 60, 1.22 / 1.27 of 300).
+template <class F>
+inline bool one_part(uint32_t N, int D, int64_t T, uint32_t most8, F &&layout)
+{
+    const uint32_t whole = (N + 63) / 64 * 64, packed = std::max(16u, (N + 3) / 4 * 4);
+    const bool brief = T < 200;
+    if (D <= 2) return N <= (brief ? 1024u : 640u) && layout(D, whole);
+    if (D <= 4) return N <= 512 ? layout(2, packed) : N <= (brief ? 960u : 768u) && layout(4, whole);
+    for (int c = D <= 12 ? 2 : 4; c <= 8; c *= 2) {
+        const uint32_t L = ((uint32_t)D + c - 1) / c;
+        if (c == 8 && (N > most8 || (uint64_t)N * D > 6500)) return false;
+        if (L > 1 && packed * L <= 1024 && layout(c, packed)) return true;
+    }
+    return false;
+}
+
+// Compute units of the current device and the most LDS a workgroup may have.
+bool gang_device(int *cus, int *lds);
 // Up to T iterations, continuing from and updating the control block (stop
 // rule included).  ctrl->gang_arrive and gang_state must be zero (launch_arm,
 // launch_gang_arm); gang_state then says whether the launch ran.

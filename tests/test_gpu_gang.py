@@ -46,7 +46,7 @@ def check(spec, cuts, tol=0.0, f_star=0.0):
     ("ackley", 321, 17, "4,64"), ("rosenbrock", 500, 33, "8,64"), ("cubic", 64, 65, "8,64"),
     ("rastrigin", 129, 47, "16,128"), ("rosenbrock", 70, 18, "16,64"), ("sphere", 33, 31, "2,16"),
     ("rosenbrock", 50, 21, "2,32"), ("ackley", 95, 13, "4,32"), ("rastrigin", 40, 101, "8,16"),
-    ("rosenbrock", 47, 70, "8,32"), ("rosenbrock", 300, 127, "64,256"), ("ackley", 300, 66, "64,256"),
+    ("rosenbrock", 47, 70, "8,32"), ("rosenbrock", 150, 19, "4,152"), ("ackley", 71, 49, "8,72"), ("cubic", 77, 1, "1,64"), ("rosenbrock", 300, 127, "64,256"), ("ackley", 300, 66, "64,256"),
     ("cubic", 130, 129, "64,64"), ("rastrigin", 129, 125, "64,128")])
 def test_gang_shapes_equal_oracle(monkeypatch, fit, N, D, shape):
     spec = wl.SwarmSpec(fit, N, D, 60, seed=N * 3 + D, shift_amplitude=1.5)
@@ -97,6 +97,83 @@ def test_gang_parameter_limits(monkeypatch, fit, name, kw):
             out.append(g.state())
     for k in ("x", "v", "p", "pf"):
         assert np.array_equal(out[0][k].view(np.uint32), out[1][k].view(np.uint32)), k
+
+
+def state64_equal(g, o):
+    st = g.state()
+    assert st["t"] == o["iters"] and st["gbest_idx"] == o["gbest_idx"]
+    for k in ("x", "v", "p", "pf"):
+        assert np.array_equal(st[k].view(np.uint64), o[k].view(np.uint64)), k
+
+
+def swarm64(sp):
+    return pso.Swarm64(sp.fitness, sp.N, sp.D, sp.box, sp.w, sp.c1, sp.c2, sp.vmax, sp.seed, shift=sp.shift)
+
+
+@pytest.mark.parametrize("fit,N,D,shape", [
+    ("cubic", 1, 1, "1,64"), ("sphere", 700, 1, "1,256"), ("rosenbrock", 1000, 2, "2,256"), ("cubic", 90, 4, "4,128"),
+    ("sphere", 3000, 3, "4,1024"), ("rosenbrock", 700, 8, "8,512"), ("cubic", 300, 15, "16,256"),
+    ("rosenbrock", 600, 31, "32,512"), ("sphere", 130, 5, "2,64"), ("cubic", 200, 6, "4,64"),
+    ("rosenbrock", 300, 33, "8,64"), ("sphere", 129, 47, "16,128"), ("rosenbrock", 150, 70, "32,128"),
+    ("rosenbrock", 50, 21, "2,32"), ("cubic", 41, 30, "4,44"), ("rosenbrock", 63, 101, "8,16")])
+def test_gang64_shapes_equal_oracle(monkeypatch, fit, N, D, shape):
+    T = 60
+    spec = wl.SwarmSpec(fit, N, D, T, seed=N * 5 + D, shift_amplitude=1.5)
+    announce(f"gang f64 {fit} N={N} D={D} shape {shape}")
+    monkeypatch.setenv("PSO64_GANG_SHAPE", shape)
+    o = oracle_swarm(spec, 8).run_f64(T)
+    with swarm64(spec) as g:
+        g.step(3)  # pending pbest positions of the grid steps before it
+        g.run(20)
+        r = g.run(T - 23)
+        assert r["gbest_fit"] == o["gbest_fit"] and r["gbest_iter"] == o["giter"]
+        state64_equal(g, o)
+
+
+@pytest.mark.parametrize("fit,N,D,tol", [("sphere", 5000, 1, 1e-12), ("sphere", 700, 2, 1e-20),
+                                         ("rosenbrock", 900, 3, 1e-4), ("sphere", 2000, 10, 1e-6), ("cubic", 200, 3, 0.0)])
+def test_gang64_blocks_and_stop_rule(fit, N, D, tol):
+    spec = wl.SwarmSpec(fit, N, D, 900, seed=5 * N + D, shift_amplitude=1.0)
+    announce(f"gang f64 stop rule {fit} N={N} D={D}")
+    for t in (tol, 0.0):
+        o = oracle_swarm(spec, 8).run_f64(900, tol=t, f_star=0.0)
+        with swarm64(spec) as g:
+            r1 = g.run(7, tol=t)
+            r2 = g.run(893, tol=t)
+            assert r1["iters"] + r2["iters"] == o["iters"] and r2["gbest_iter"] == o["giter"]
+            state64_equal(g, o)
+
+
+@pytest.mark.parametrize("fit", ["rastrigin", "ackley"])
+@pytest.mark.parametrize("N,D,shape", [(300, 1, "1,64"), (300, 2, "2,128"), (200, 7, "2,16"), (200, 30, "4,64"),
+                                       (200, 30, "16,64"), (100, 61, "8,16"), (200, 64, "32,64")])
+def test_gang64_transcendental_equals_grid_steps(monkeypatch, fit, N, D, shape):
+    """Rastrigin and Ackley call the device's cos and exp: the gang's bits are
+    the grid steps'."""
+    spec = wl.SwarmSpec(fit, N, D, 50, seed=N + D, shift_amplitude=1.5)
+    announce(f"gang f64 {fit} N={N} D={D} shape {shape}")
+    out = []
+    for env in (shape, None):
+        if env:
+            monkeypatch.setenv("PSO64_GANG_SHAPE", env)
+        else:
+            monkeypatch.setenv("PSO64_PATH", "grid")
+        with swarm64(spec) as g:
+            g.run(50)
+            out.append(g.state())
+    for k in ("x", "v", "p", "pf"):
+        assert np.array_equal(out[0][k].view(np.uint64), out[1][k].view(np.uint64)), k
+    assert out[0]["gbest_idx"] == out[1]["gbest_idx"]
+
+
+@pytest.mark.parametrize("box", [(0.0, 7.0), (-7.0, -0.0), (-0.0, 7.0)])
+def test_gang64_zero_bounds(box):
+    spec = wl.SwarmSpec("sphere", 700, 6, 60, seed=3, box=box)
+    announce(f"gang f64 bounds {box}")
+    o = oracle_swarm(spec, 8).run_f64(60)
+    with swarm64(spec) as g:
+        g.run(60)
+        state64_equal(g, o)
 
 
 def test_gangs_that_exclude_each_other(monkeypatch):
