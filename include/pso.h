@@ -348,7 +348,11 @@ int pso_batch_run_static(const pso_desc *descs, int64_t count, pso_result *resul
  * the same swarm sizes and iteration limits on the same device, else 1024
  * lanes with 158 KiB staged (less for D above 64: the LDS also holds
  * 2 x D floats) if every swarm fits that, else 256 lanes, the
- * full capacity, 2^17 updates per part, streamed.  The co-resident capacity
+ * full capacity, 2^17 updates per part, streamed.  Under a shape of 1024
+ * lanes and that much staged state, a batch whose swarms all have D <= 64 and
+ * ordinary parameters, and that fills the device, holds its parts in registers
+ * instead of LDS: up to four workgroups of 256 lanes for each of the shape's
+ * (PSO_BATCH_REGISTERS=0 in the environment of pso_batch_create: never).  The co-resident capacity
  * is three quarters of the occupancy bound streamed and all but 8 compute
  * units' worth staged: a batch sharing the device with other long-running
  * kernels may find its parts not co-resident, which its bounded waits report

@@ -335,6 +335,14 @@ __global__ void __launch_bounds__(RUN_LANES) k_block_run(SwarmArgs a, long long 
 // queue order with a part not yet dequeued has all its earlier parts either
 // running or waiting for it, and every swarm before it has all its parts.
 // ---------------------------------------------------------------------------
+// Clears a meeting's tagged words: the keys, then the candidate positions.
+// One wavefront.
+__device__ __forceinline__ void clear_meeting(const BatchItem &it)
+{
+    unsigned long long *const end = reinterpret_cast<unsigned long long *>(it.cand_pos) + (size_t)2 * it.parts * it.a.D;
+    for (unsigned long long *w = it.cand_key + threadIdx.x; w < end; w += 64) *w = 0ull;
+}
+
 __global__ void __launch_bounds__(64) k_batch_reset(const BatchItem *items, BatchResult *results, uint32_t count,
                                                      unsigned int *next)
 {
@@ -353,12 +361,7 @@ __global__ void __launch_bounds__(64) k_batch_reset(const BatchItem *items, Batc
             items[i].gang->err = 0u;
         }
     }
-    if (items[i].parts > 1) { // the meeting's tagged words (keys, then candidate positions)
-        const size_t nk = (size_t)4 * items[i].parts, np = (size_t)2 * items[i].parts * items[i].a.D;
-        for (size_t w = threadIdx.x; w < nk; w += 64) items[i].cand_key[w] = 0ull;
-        unsigned long long *pw = reinterpret_cast<unsigned long long *>(items[i].cand_pos);
-        for (size_t w = threadIdx.x; w < np; w += 64) pw[w] = 0ull;
-    }
+    if (items[i].parts > 1) clear_meeting(items[i]);
 }
 
 __global__ void k_counter_reset(unsigned int *next)
@@ -954,6 +957,12 @@ __global__ void __launch_bounds__(LANES) k_batch_staged(const BatchItem *items, 
 uint32_t staged_parts(uint64_t N, int D, int fitness, int stage_kib, int grid_cap)
 {
     if (stage_kib < 1 || D < 1 || N < 1) return 0;
+    if (stage_kib == STAGE_REGISTERS) {
+        if (D > RESIDENT_MAX_D) return 0;
+        if (N > (uint64_t)MAX_STAGED_PARTS * RESIDENT_LANES) return 0;
+        const uint32_t parts = resident_split(N, D).parts;
+        return parts > MAX_STAGED_PARTS || parts > (uint32_t)std::max(1, grid_cap) ? 0 : parts;
+    }
     const uint64_t qmax = (uint64_t)stage_kib * 1024 / staged_quad_bytes(D, fitness);
     if (qmax < 1) return 0;
     const uint64_t nq = (N + 3) / 4;
@@ -1099,12 +1108,7 @@ __global__ void __launch_bounds__(64) k_upload(const UploadRec *recs, uint32_t n
         state[u.slot] = u.state;
         if (u.reset_gang && u.item.gang) *u.item.gang = GangSync{};
     }
-    if (u.reset_gang && u.item.gang) { // the meeting's tagged words
-        const size_t nk = (size_t)4 * u.item.parts, np = (size_t)2 * u.item.parts * u.item.a.D;
-        for (size_t w = threadIdx.x; w < nk; w += 64) u.item.cand_key[w] = 0ull;
-        unsigned long long *pw = reinterpret_cast<unsigned long long *>(u.item.cand_pos);
-        for (size_t w = threadIdx.x; w < np; w += 64) pw[w] = 0ull;
-    }
+    if (u.reset_gang && u.item.gang) clear_meeting(u.item);
     float *shift = const_cast<float *>(u.item.a.shift);
     for (int d = threadIdx.x; d < u.item.a.D; d += 64) shift[d] = pool[u.shift_at + d];
 }
@@ -1143,8 +1147,12 @@ hipError_t launch_batch(const BatchItem *items, const BatchEntry *entries, Batch
                         unsigned int *next, int maxD, int grid, int lanes, long long chunk, long long iter_cap,
                         hipStream_t stream, BatchResult *out_state, float *out_pos, unsigned int *err, int stage_kib)
 {
-    if (!batch_lanes_supported(lanes, stage_kib > 0)) return hipErrorInvalidValue;
+    if (stage_kib == STAGE_REGISTERS ? lanes != RESIDENT_LANES : !batch_lanes_supported(lanes, stage_kib > 0))
+        return hipErrorInvalidValue;
     hipLaunchKernelGGL(k_counter_reset, dim3(1), dim3(64), 0, stream, next);
+    if (stage_kib == STAGE_REGISTERS)
+        return launch_batch_resident(items, entries, results, count, next, grid, chunk, iter_cap, stream, out_state,
+                                     out_pos, maxD, err);
     if (stage_kib > 0) {
         if (lanes == 1024)
             return launch_staged<1024>(items, entries, results, count, next, maxD, grid, chunk, iter_cap, stream,
@@ -1175,11 +1183,18 @@ hipError_t launch_batch(const BatchItem *items, const BatchEntry *entries, Batch
 
 hipError_t batch_capacity(int maxD, int lanes, int *workgroups, int stage_kib)
 {
-    if (!batch_lanes_supported(lanes, stage_kib > 0)) return hipErrorInvalidValue;
-    const size_t lds = batch_dynamic_lds(maxD, stage_kib);
+    if (stage_kib == STAGE_REGISTERS ? lanes != RESIDENT_LANES : !batch_lanes_supported(lanes, stage_kib > 0))
+        return hipErrorInvalidValue;
     int per_cu = 0, dev = 0, cus = 0, lds_max = 0;
     hipError_t e;
     if ((e = hipGetDevice(&dev)) != hipSuccess) return e;
+    if (stage_kib == STAGE_REGISTERS) {
+        if ((e = resident_occupancy(&per_cu)) != hipSuccess) return e;
+        if ((e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev)) != hipSuccess) return e;
+        *workgroups = std::min(per_cu, RESIDENT_PER_CU) * std::max(1, cus - 8); // the staged kernel's margin, below
+        return hipSuccess;
+    }
+    const size_t lds = batch_dynamic_lds(maxD, stage_kib);
     if (stage_kib > 0) {
         if ((e = hipDeviceGetAttribute(&lds_max, hipDeviceAttributeMaxSharedMemoryPerBlock, dev)) != hipSuccess)
             return e;

@@ -9,6 +9,52 @@ namespace pso {
 constexpr uint32_t MAX_PARTS = 64;         // workgroups one streamed batched swarm may span
 constexpr uint32_t MAX_STAGED_PARTS = 512; // workgroups one LDS-staged batched swarm may span
 
+// Value of a shape's stage_kib for parts that hold their particles in vector
+// registers (pso_resident.hip): 256 lanes, L of them to a particle, each with
+// cs dimensions; P particles of a part, a multiple of 64, so that the chunk is
+// the same over a wavefront.  Small swarms take more lanes of fewer dimensions,
+// and 33 to 48 dimensions four lanes rather than three, so that their parts
+// fill their workgroups.
+constexpr int STAGE_REGISTERS = 1 << 20;
+constexpr int RESIDENT_LANES = 256, RESIDENT_C = 16, RESIDENT_MAX_D = 64;
+constexpr int RESIDENT_PER_CU = 4;    // workgroups that share a compute unit
+constexpr uint32_t RESIDENT_LINE = 8; // 64-bit words between the key words of two parts
+struct ResidentSplit {
+    uint32_t L, cs, P, parts;
+};
+__host__ __device__ inline ResidentSplit resident_split(uint64_t N, int D)
+{
+    uint32_t L = ((uint32_t)D + RESIDENT_C - 1) / RESIDENT_C;
+    const uint32_t wide = N <= 64 ? 4u : N <= 128 ? 2u : 1u, most = (uint32_t)D / 4;
+    if (L < wide && most > L) L = wide < most ? wide : most;
+    if (L == 3) L = 4;
+    uint32_t cs = ((uint32_t)D + L - 1) / L;
+    cs += cs & 1u;
+    L = ((uint32_t)D + cs - 1) / cs;
+    const uint32_t P = L == 1 ? 256u : L == 2 ? 128u : 64u;
+    return ResidentSplit{L, cs, P, (uint32_t)((N + P - 1) / P)};
+}
+// Whether holding a swarm of `parts` parts in registers beats staging it in
+// LDS, in a launch of `total` parts in all on `grid` workgroups (200
+// iterations of Rastrigin; registers against LDS in ms):
+//  - Parts that have a compute unit to themselves: a swarm of one or two parts
+//    is faster on the 1024 lanes of the LDS-staged kernel (one swarm, D = 30,
+//    N = 200: 1.17 against 1.00; N = 16: 0.66 / 0.48) unless D <= 4 (N = 200,
+//    D = 2: 0.78 of it), as is one that is several parts here and one there at
+//    D <= 2 (N = 1000, D = 1: 0.42 / 0.35).  Larger swarms gain from being
+//    split further (N = 4000, D = 10: 0.59 of LDS's time, D = 2: 0.41;
+//    N = 200, D = 48: 0.95).
+//  - Parts that outnumber the workgroups at D <= 4: a register part holds 256
+//    particles, an LDS part thousands, and meets as often (300 swarms of
+//    N = 16000, D = 1: 18.0 / 9.4; D = 4: 20.0 / 18.3; D = 6: 0.88 of it).
+//  - Else registers: 300 swarms of N = 1000, D = 30: 0.71 of LDS's time;
+//    N = 200, D = 30: 0.91.
+inline bool registers_pay(uint64_t N, int D, uint64_t parts, uint64_t total, int grid)
+{
+    if (total <= (uint64_t)(grid / RESIDENT_PER_CU)) return D <= 2 ? N <= 256 || N > 1024 : D <= 4 || N > 256 || parts > 2;
+    return !(D <= 4 && parts > 1 && total > (uint64_t)grid);
+}
+
 // Meeting point of the parts of one swarm (parts > 1): each part posts its
 // workgroup-minimum key and, if it has one, that particle's position into the
 // slots of the step's parity, as words tagged with the step (cand_key,
@@ -22,8 +68,9 @@ struct GangSync {
 
 // One swarm of a batch: its state view (pointers into the batch's memory,
 // parameters, Philox key), its run limits and, when split into parts, the
-// parts' meeting point: cand_key[2][parts][2] (a key's low and high halves)
-// and cand_pos[2][parts][D] (one coordinate's bits), 64-bit words whose high
+// parts' meeting point: cand_key[2][parts][2] (a key's low and high halves;
+// of parts held in registers [2][parts][RESIDENT_LINE]) and
+// cand_pos[2][parts][D] (one coordinate's bits), 64-bit words whose high
 // halves carry the step.
 struct BatchItem {
     SwarmArgs a;
@@ -62,6 +109,7 @@ bool batch_lanes_supported(int lanes, bool staged = false);
 // LDS bytes one staged particle quad takes: x, v, p and the fitness terms of
 // each of D dimensions, its pbest fitness and pending marks.
 size_t staged_quad_bytes(int D, int fitness);
+
 // Parts of a swarm under an LDS-staged shape (each part's quads fit
 // stage_kib KiB), or 0 if it would need more than MAX_STAGED_PARTS or
 // grid_cap workgroups.
@@ -77,6 +125,24 @@ uint32_t parts_for(uint64_t N, int D, int grid_cap, const BatchShape &shape);
 size_t gang_bytes(uint32_t parts, int D);
 // Points the item's gang fields into a region of gang_bytes(parts, D).
 void bind_gang(BatchItem *it, void *region, uint32_t parts);
+// The same for parts held in registers: each part's key words on a line of
+// their own.
+inline size_t resident_gang_bytes(uint32_t parts, int D)
+{
+    const size_t words = sizeof(unsigned long long) * 2 * parts * (size_t)(RESIDENT_LINE + D);
+    return parts <= 1 ? 0 : 256 + ((words + 255) & ~size_t(255));
+}
+inline void bind_resident_gang(BatchItem *it, void *region, uint32_t parts)
+{
+    it->parts = parts < 1 ? 1 : parts;
+    it->gang = nullptr;
+    it->cand_key = nullptr;
+    it->cand_pos = nullptr;
+    if (it->parts == 1) return;
+    it->gang = static_cast<GangSync *>(region);
+    it->cand_key = reinterpret_cast<unsigned long long *>(static_cast<char *>(region) + 256);
+    it->cand_pos = reinterpret_cast<float *>(it->cand_key + 2 * (size_t)parts * RESIDENT_LINE);
+}
 
 // Loop state (and result) of one batched swarm, kept in device memory
 // between launches; the gbest position is kept in a.gpos.
@@ -120,12 +186,20 @@ hipError_t launch_batch_reset(const BatchItem *items, BatchResult *results, uint
 // any other launch running concurrently) and every swarm's parts <= grid.
 // Optionally writes each swarm's state to out_state[out] and its gbest
 // position to out_pos[out*maxD ..]; device errors set *err.
-// stage_kib > 0 runs the LDS-staged kernel (every item's parts must come from
-// staged_parts for the same stage_kib).
+// stage_kib > 0 runs the LDS-staged kernel, STAGE_REGISTERS the one that holds
+// parts in registers (every item's parts must come from staged_parts for the
+// same stage_kib).
 hipError_t launch_batch(const BatchItem *items, const BatchEntry *entries, BatchResult *results, uint32_t count,
                         unsigned int *next, int maxD, int grid, int lanes, long long chunk, long long iter_cap,
                         hipStream_t stream, BatchResult *out_state, float *out_pos, unsigned int *err,
                         int stage_kib = 0);
+// launch_batch for STAGE_REGISTERS, the workgroups of it a compute unit holds,
+// and its LDS.
+hipError_t launch_batch_resident(const BatchItem *items, const BatchEntry *entries, BatchResult *results, uint32_t count,
+                                 unsigned int *next, int grid, long long chunk, long long iter_cap, hipStream_t stream,
+                                 BatchResult *out_state, float *out_pos, int pos_stride, unsigned int *err);
+hipError_t resident_occupancy(int *per_cu);
+size_t resident_lds();
 // Workgroups of `lanes` lanes of the batched kernel (LDS-staged with
 // stage_kib KiB if > 0) that are safely co-resident: three quarters of the
 // occupancy bound streamed, all but 8 compute units' worth staged; 0 if the

@@ -676,12 +676,14 @@ struct pso_batch {
     uint32_t n_entries = 0;
     uint32_t n_first = 0;  // entries of the first kernel (all of them unless some swarms stream after it)
     int grid_rest = 0;     // workgroups of the second (streamed) kernel
+    int grid_registers = 0; // workgroups if the parts are held in registers, else 0
     pso::BatchResult *d_results = nullptr;
     unsigned int *d_next = nullptr;
     unsigned int *d_err = nullptr;
     std::vector<pso::BatchItem> items; // host copy (device pointers inside)
     std::vector<char *> gang;          // each swarm's gang region (sized for max_parts)
     std::vector<uint32_t> max_parts;
+    bool registers = false;            // every swarm's parts may be held in registers
     std::vector<uint64_t> N;
     std::vector<int> D;
     std::vector<long long> max_iter;
@@ -747,6 +749,46 @@ std::vector<pso::BatchShape> tuner_candidates(int maxD)
     return c;
 }
 
+// Whether a shape asks for whole compute units (the staged default, and the
+// tuner's shape of 1024 lanes): a batch whose swarms all suit it then holds
+// their parts in registers, four 256-lane workgroups in place of each
+// 1024-lane one.
+bool whole_unit_shape(const pso::BatchShape &sh, int maxD)
+{
+    return sh.lanes == pso::DEFAULT_STAGED_SHAPE.lanes && sh.stage_kib > 0 && sh.stage_kib >= staged_kib_fitting(maxD, 1);
+}
+
+// Whether a batch's parts are held in registers where its shape allows: the
+// short forms are exact for every swarm, every swarm's parts fit a launch and
+// the work queue stays within a batch's bound (every swarm, so that a launch
+// is one kernel), and the swarm with the most work gains.
+// PSO_BATCH_REGISTERS=0 in the environment: never.
+bool registers_suit(const pso_desc *descs, int64_t count, int grid)
+{
+    const char *env = getenv("PSO_BATCH_REGISTERS");
+    if (env && !strcmp(env, "0")) return false;
+    uint64_t total = 0;
+    double most = -1.0;
+    int64_t heavy = 0;
+    for (int64_t i = 0; i < count; ++i) {
+        const pso_desc &d = descs[i];
+        float shift_max = 0.0f;
+        for (int q = 0; d.shift && q < d.D; ++q) shift_max = std::max(shift_max, std::fabs(d.shift[q]));
+        if (!pso::short_forms_exact(d.fitness_id, d.bounds[0], d.bounds[1], d.c1, d.c2, shift_max, false) ||
+            !pso::staged_parts((uint64_t)d.N, d.D, d.fitness_id, pso::STAGE_REGISTERS, grid))
+            return false;
+        total += pso::resident_split((uint64_t)d.N, d.D).parts;
+        const double work = double(d.N) * d.D * double(d.max_iter + 1);
+        if (work > most) {
+            most = work;
+            heavy = i;
+        }
+    }
+    const pso_desc &h = descs[heavy];
+    return total <= MAX_BATCH_ENTRIES / 2 &&
+           pso::registers_pay((uint64_t)h.N, h.D, pso::resident_split((uint64_t)h.N, h.D).parts, total, grid);
+}
+
 // Process-wide choices of the autotuner, by batch signature and device.
 std::mutex g_tuned_mu;
 std::map<std::pair<uint64_t, int>, pso::BatchShape> g_tuned;
@@ -770,9 +812,20 @@ int batch_configure(pso_batch *b, const pso::BatchShape &sh)
     const pso::BatchShape stream_sh = staged ? pso::BatchShape{256, 0, 1LL << 17, 0} : sh;
     int grid_s = grid;
     if (staged) HIP_TRY(shape_grid(b->maxD, stream_sh, &grid_s));
+    int grid_r = 0;
+    if (b->registers && whole_unit_shape(sh, b->maxD)) {
+        HIP_TRY(pso::batch_capacity(b->maxD, pso::RESIDENT_LANES, &grid_r, pso::STAGE_REGISTERS));
+        grid_r = std::min(grid_r, grid * pso::RESIDENT_PER_CU);
+        for (int64_t i = 0; i < b->count && grid_r > 0; ++i) // a smaller grid than the capacity may not hold a swarm
+            if (!pso::staged_parts(b->N[i], b->D[i], b->items[i].fitness, pso::STAGE_REGISTERS, grid_r)) grid_r = 0;
+    }
     std::vector<uint32_t> parts(b->count);
     std::vector<char> streamed(b->count, 0);
     for (int64_t i = 0; i < b->count; ++i) {
+        if (grid_r > 0) {
+            parts[i] = pso::staged_parts(b->N[i], b->D[i], b->items[i].fitness, pso::STAGE_REGISTERS, grid_r);
+            continue;
+        }
         if (staged) {
             parts[i] = pso::staged_parts(b->N[i], b->D[i], b->items[i].fitness, sh.stage_kib, grid);
             if (parts[i] > 0 && parts[i] <= b->max_parts[i]) continue;
@@ -782,7 +835,7 @@ int batch_configure(pso_batch *b, const pso::BatchShape &sh)
     }
     uint64_t n_entries = 0, n_first = 0;
     for (int64_t i = 0; i < b->count; ++i) {
-        pso::bind_gang(&b->items[i], b->gang[i], parts[i]);
+        (grid_r > 0 ? pso::bind_resident_gang : pso::bind_gang)(&b->items[i], b->gang[i], parts[i]);
         n_entries += parts[i];
         if (!streamed[i]) n_first += parts[i];
     }
@@ -803,7 +856,9 @@ int batch_configure(pso_batch *b, const pso::BatchShape &sh)
     HIP_TRY(hipMemcpy(b->d_entries, entries.data(), sizeof(pso::BatchEntry) * n_entries, hipMemcpyHostToDevice));
     b->n_entries = (uint32_t)n_entries;
     b->n_first = (uint32_t)n_first;
-    b->grid = (int)std::min<uint64_t>(n_first, (uint64_t)grid);
+    b->grid_registers = (int)std::min<uint64_t>(n_first, (uint64_t)grid_r);
+    b->grid = grid_r > 0 ? (b->grid_registers + pso::RESIDENT_PER_CU - 1) / pso::RESIDENT_PER_CU
+                         : (int)std::min<uint64_t>(n_first, (uint64_t)grid);
     b->grid_rest = (int)std::min<uint64_t>(n_entries - n_first, (uint64_t)grid_s);
     b->shape = sh;
     drop_graph(b); // the captured launch had the old grid and lanes
@@ -813,7 +868,11 @@ int batch_configure(pso_batch *b, const pso::BatchShape &sh)
 int batch_launch_iters(pso_batch *b, long long iter_cap, bool reset)
 {
     if (reset) HIP_TRY(pso::launch_batch_reset(b->d_items, b->d_results, (uint32_t)b->count, b->d_next, b->stream));
-    if (b->n_first > 0)
+    if (b->grid_registers > 0)
+        HIP_TRY(pso::launch_batch(b->d_items, b->d_entries, b->d_results, b->n_first, b->d_next, b->maxD,
+                                  b->grid_registers, pso::RESIDENT_LANES, (long long)1 << 62, iter_cap, b->stream,
+                                  nullptr, nullptr, b->d_err, pso::STAGE_REGISTERS));
+    else if (b->n_first > 0)
         HIP_TRY(pso::launch_batch(b->d_items, b->d_entries, b->d_results, b->n_first, b->d_next, b->maxD, b->grid,
                                   b->shape.lanes, (long long)1 << 62, iter_cap, b->stream, nullptr, nullptr, b->d_err,
                                   b->shape.stage_kib));
@@ -854,6 +913,10 @@ int pso_batch_create(const pso_desc *descs, int64_t count, void *hip_stream, pso
         std::vector<size_t> off(count), goff(count);
         std::vector<uint32_t> maxp(count);
         size_t total = 0;
+        int reg_grid = 0;
+        if (pso::batch_capacity(maxD, pso::RESIDENT_LANES, &reg_grid, pso::STAGE_REGISTERS) != hipSuccess)
+            return fail(PSO_EDEVICE, "device query failed");
+        const bool registers = registers_suit(descs, count, reg_grid);
         uint64_t max_entries = 0, sig = 1469598103934665603ull;
         auto mix = [&](uint64_t v) { sig = (sig ^ v) * 1099511628211ull; };
         mix((uint64_t)count);
@@ -865,11 +928,12 @@ int pso_batch_create(const pso_desc *descs, int64_t count, void *hip_stream, pso
                 mp = std::max(mp, cands[c].stage_kib > 0
                                       ? pso::staged_parts((uint64_t)d.N, d.D, d.fitness_id, cands[c].stage_kib, cand_grid[c])
                                       : pso::parts_for((uint64_t)d.N, d.D, cand_grid[c], cands[c]));
+            const uint32_t rp = registers ? pso::resident_split((uint64_t)d.N, d.D).parts : 0u;
             maxp[i] = mp;
             off[i] = total;
             goff[i] = total + lay[i].total;
-            total += lay[i].total + pso::gang_bytes(mp, d.D);
-            max_entries += mp;
+            total += lay[i].total + std::max(pso::gang_bytes(mp, d.D), pso::resident_gang_bytes(rp, d.D));
+            max_entries += std::max(mp, rp);
             // bounded before anything is allocated: the work queue's entry
             // count is a 32-bit value, and no device holds this many bytes
             if (total > MAX_BATCH_BYTES)
@@ -907,6 +971,7 @@ int pso_batch_create(const pso_desc *descs, int64_t count, void *hip_stream, pso
         b->items.resize(count);
         b->gang.resize(count);
         b->max_parts = maxp;
+        b->registers = registers;
         b->N.resize(count);
         b->D.resize(count);
         b->max_iter.resize(count);

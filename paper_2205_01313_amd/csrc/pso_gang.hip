@@ -56,50 +56,12 @@
 #include <cstring>
 
 #include "pso_gang.hpp"
+#include "pso_gang_device.hpp"
 #include "pso_quad.hpp"
 
 namespace pso {
 
 constexpr unsigned long long NO_COMB = ~0ull;
-
-// cos(2 pi z) for |2 z| < 2^22: cospi_f32's operations without the cases of
-// large and non-finite arguments (NaN gives NaN).  2z + 1.5 2^23 rounds 2z to
-// an integer and leaves its parity in the lowest bit.
-__device__ __forceinline__ float cos2pi_small(float z)
-{
-    const float t = __builtin_fmaf(z, 2.0f, 0x1.8p23f);
-    const float n = t - 0x1.8p23f;
-    const float a = __builtin_fabsf(__builtin_fmaf(z, 2.0f, -n));
-    const bool lo = a <= 0.25f;
-    const float cc = cos_pi_series(a), ss = sin_pi_series(0.5f - a);
-    return __uint_as_float(__float_as_uint(lo ? cc : ss) ^ (__float_as_uint(t) << 31));
-}
-
-// The fitness term(s) of one dimension, and Rosenbrock's of a pair: the
-// expressions Fitness<FIT>::add evaluates.
-template <int FIT>
-__device__ __forceinline__ float gang_term(float z)
-{
-    if constexpr (FIT == F_RASTRIGIN) return z * z - 10.0f * cos2pi_small(z);
-    else if constexpr (FIT == F_CUBIC) {
-        const float z2 = z * z;
-        return ((z2 * z - 0.8f * z2) - 1000.0f * z) + 8000.0f;
-    } else return z * z; // Sphere, Ackley's first word
-}
-
-__device__ __forceinline__ float rosen_term(float z, float zp)
-{
-    const float a = z - zp * zp;
-    const float b = 1.0f - zp;
-    return 100.0f * (a * a) + b * b;
-}
-
-// Clamp to [lo, hi] in two instructions; equals the comparisons for every
-// value the gang accepts (gang_accepts: signs of zero).
-__device__ __forceinline__ float clamp_pos(float v, float lo, float hi)
-{
-    return __builtin_elementwise_minimum(__builtin_elementwise_maximum(v, lo), hi);
-}
 
 // A lane's chunk; of p, the first C - PL dimensions (the others are in LDS).
 template <int C, int PL>
@@ -645,20 +607,7 @@ bool gang_accepts(int fitness, const SwarmArgs &a, float shift_max, bool state_s
 {
     const char *env = getenv("PSO_GANG");
     if (env && !strcmp(env, "0")) return false;
-    if (fitness < F_SPHERE || fitness > F_CUBIC) return false;
-    // c 2^-24 must be exact
-    auto scales = [](float c) { return c == 0.0f || std::fabs(c) >= 0x1p-100f; };
-    if (!scales(a.c1) || !scales(a.c2)) return false;
-    // clamp_pos equals the comparisons unless a bound is a zero that a zero
-    // of the other sign can meet: x is never -0 with lo = +0 (Step 1 gives
-    // none, and x + v is -0 only if x is) unless the caller set the state
-    if (a.hi == 0.0f && std::signbit(a.hi)) return false;
-    if (a.lo == 0.0f && !std::signbit(a.lo) && state_set) return false;
-    // cos2pi_small's range
-    if ((fitness == F_RASTRIGIN || fitness == F_ACKLEY) &&
-        !(std::max(std::fabs(a.lo), std::fabs(a.hi)) + shift_max < 0x1p20f))
-        return false;
-    return true;
+    return short_forms_exact(fitness, a.lo, a.hi, a.c1, a.c2, shift_max, state_set);
 }
 
 size_t gang_words(uint32_t parts, int D)

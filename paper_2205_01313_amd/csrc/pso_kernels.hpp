@@ -6,6 +6,9 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include <algorithm>
+#include <cmath>
+
 namespace pso {
 
 constexpr int HIST_CAP = 8192; // gbest keys kept per swarm (ring, power of two)
@@ -100,6 +103,25 @@ constexpr uint64_t ROW_ALIGN = 64;
 // control = false leaves out the control block and history (batched swarms).
 Layout layout_of(uint64_t N, int D, bool control = true);
 SwarmArgs bind(void *base, const Layout &L, uint64_t N, int D);
+
+// Whether the shorter instruction sequences of the register-resident kernels
+// compute the other kernels' bits for these parameters (shift_max: largest
+// magnitude of the shift vector; state_set: the caller set the state):
+//   - c1 2^-24 and c2 2^-24 must be exact (the uniforms' scale is folded in);
+//   - a clamp by maximum and minimum equals the comparisons unless a bound is a
+//     zero that a zero of the other sign can meet: x is never -0 with lo = +0
+//     (Step 1 gives none, and x + v is -0 only if x is) unless the caller set
+//     the state;
+//   - the cosine's short argument reduction needs |2 z| < 2^22.
+inline bool short_forms_exact(int fitness, float lo, float hi, float c1, float c2, float shift_max, bool state_set)
+{
+    auto scales = [](float c) { return c == 0.0f || std::fabs(c) >= 0x1p-100f; };
+    if (fitness < 0 || fitness > 4 || !scales(c1) || !scales(c2)) return false;
+    if (hi == 0.0f && std::signbit(hi)) return false;
+    if (lo == 0.0f && !std::signbit(lo) && state_set) return false;
+    const bool cosine = fitness == 1 || fitness == 3; // Rastrigin, Ackley
+    return !cosine || std::max(std::fabs(lo), std::fabs(hi)) + shift_max < 0x1p20f;
+}
 
 // Launchers; all enqueue on `stream` and return the launch status.
 hipError_t launch_reset(const SwarmArgs &a, hipStream_t stream);

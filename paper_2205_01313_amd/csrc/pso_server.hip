@@ -46,6 +46,10 @@ double ms_since(Clock::time_point t0, Clock::time_point t1)
     return std::chrono::duration<double, std::milli>(t1 - t0).count();
 }
 
+// Where a request's state is during a launch: in device memory, in LDS
+// (copied in and out once) or in registers (the same).
+enum Kind { STREAMED, STAGED, REGISTERS, KINDS };
+
 struct Req {
     uint64_t ticket = 0;
     pso_desc d{};
@@ -62,7 +66,7 @@ struct Req {
     std::vector<float> gpos;
     double us_per_iter = 0.0; // measured time of one iteration on the device (0: not yet)
     long long prev_iters = 0;
-    bool staged = false;      // runs in LDS-staged launches (else streamed ones)
+    int kind = STREAMED;      // of the launches it runs in
 };
 
 #ifndef PSO_SERVER_STREAMS
@@ -94,14 +98,19 @@ constexpr uint32_t MAX_SLICE_ITERS = 4096;
 constexpr int MAX_SERVER_D = 4096; // LDS of a launch is sized for the largest D it lists
 // LDS-staged launches: one 1024-lane workgroup per compute unit with 158 KiB
 // of staged state, which leaves room for the gbest position and shift of
-// D <= SERVER_STAGE_MAX_D in the 160 KiB.  A request of such D whose staged
-// parts fit a launch runs staged (its state in LDS for each launch), others
-// streamed; each launch is of one kind, the kind of the longest-waiting
-// ready request.  PSO_SERVER_STAGED=0 in the environment streams every
-// request.
+// D <= SERVER_STAGE_MAX_D in the 160 KiB.  A request of such D runs with its
+// state in registers for each launch if the short forms are exact for it and
+// its parts fit a launch (four 256-lane workgroups per compute unit), else
+// staged in LDS if those parts fit, others streamed; each launch is of one
+// kind.  PSO_SERVER_STAGED=0 in
+// the environment streams every request, PSO_BATCH_REGISTERS=0 holds none in
+// registers.
 constexpr int SERVER_STAGE_LANES = 1024;
 constexpr int SERVER_STAGE_KIB = 158;
 constexpr int SERVER_STAGE_MAX_D = 64;
+static_assert(SERVER_STAGE_MAX_D <= pso::RESIDENT_MAX_D, "a launch of either kind takes these D");
+constexpr int KIND_LANES[KINDS] = {pso::DEFAULT_BATCH_SHAPE.lanes, SERVER_STAGE_LANES, pso::RESIDENT_LANES};
+constexpr int KIND_STAGE[KINDS] = {0, SERVER_STAGE_KIB, pso::STAGE_REGISTERS};
 
 } // namespace
 
@@ -110,9 +119,10 @@ struct pso_server {
     size_t budget = 0;
     long long chunk = 1LL << 40; // at most this many particle-dimension updates per swarm and launch
     int max_slots = 0;
-    int grid_cap = 1;            // parts of a streamed swarm at most: half the co-resident workgroups
-    int grid_cap_staged = 0;     // the same for a staged swarm (0: staging off)
-    int launch_cap_staged = 0;   // workgroups of a staged launch (a streamed one has grid_cap)
+    // of each kind: parts of a swarm at most, half the co-resident workgroups
+    // (0: no launches of the kind), and workgroups of a launch
+    int grid_cap[KINDS] = {1, 0, 0};
+    int launch_cap[KINDS] = {1, 0, 0};
     double ticks_per_us = 100.0; // device wall clock
     double slice_us = SLICE_US_DEFAULT;
     int launch_waves = LAUNCH_WAVES_DEFAULT;
@@ -227,7 +237,7 @@ pso::BatchItem make_item(pso_server *s, const Req &r)
     it.max_iter = r.d.max_iter;
     it.tol = r.d.tol;
     it.fstar = r.d.f_star;
-    pso::bind_gang(&it, static_cast<char *>(s->base) + r.off + L.total, r.parts);
+    (r.kind == REGISTERS ? pso::bind_resident_gang : pso::bind_gang)(&it, static_cast<char *>(s->base) + r.off + L.total, r.parts);
     return it;
 }
 
@@ -278,28 +288,35 @@ bool expire_deadlines(pso_server *s)
     return any;
 }
 
-// Launches one chunk on stream k over ready swarms of one kind (staged or
-// streamed): the kind of the ready swarm submitted first, and of that kind
-// the longest-waiting swarms whose parts fit the launch's workgroups.
+// Launches one chunk on stream k over ready swarms of one kind: the kind of
+// the ready swarm submitted first among those whose kind no other stream runs
+// (among all if there is none), so that no kind waits until every older
+// request of another has ended; and of that kind the longest-waiting swarms
+// whose parts fit the launch's workgroups.
 bool launch_ready(pso_server *s, int k)
 {
     if (s->ready.empty()) return true;
     hipStream_t st = s->st[k];
     const Req *first = s->slot_req[s->ready[0]];
-    for (int slot : s->ready)
-        if (s->slot_req[slot]->t_submit < first->t_submit) first = s->slot_req[slot];
-    const bool staged = first->staged;
+    bool running[KINDS] = {};
+    for (int j = 0; j < STREAMS; ++j)
+        if (!s->inflight[j].empty()) running[s->slot_req[s->inflight[j][0]]->kind] = true;
+    for (int slot : s->ready) {
+        const Req *r = s->slot_req[slot];
+        if (running[r->kind] != running[first->kind] ? running[first->kind] : r->t_submit < first->t_submit) first = r;
+    }
+    const int kind = first->kind;
     // the longest-waiting swarms of that kind, at most launch_waves parts per
     // workgroup, so that a launch lasts about that many slices and the two
     // streams take turns
-    const int grid_cap = staged ? s->launch_cap_staged : s->grid_cap;
+    const int grid_cap = s->launch_cap[kind];
     std::stable_sort(s->ready.begin(), s->ready.end(),
                      [&](int x, int y) { return s->slot_req[x]->t_submit < s->slot_req[y]->t_submit; });
     std::vector<int> sel, rest;
     uint64_t parts = 0;
     for (int slot : s->ready) {
         const Req *r = s->slot_req[slot];
-        if (r->staged == staged && parts + r->parts <= (uint64_t)grid_cap * s->launch_waves) {
+        if (r->kind == kind && parts + r->parts <= (uint64_t)grid_cap * s->launch_waves) {
             sel.push_back(slot);
             parts += r->parts;
         } else {
@@ -424,8 +441,8 @@ bool launch_ready(pso_server *s, int k)
     }
     const int grid = std::min<int>((int)ne, grid_cap);
     if (pso::launch_batch(s->d_items, s->d_entries[k], s->d_state, ne, s->d_next[k], maxD, grid,
-                          staged ? SERVER_STAGE_LANES : pso::DEFAULT_BATCH_SHAPE.lanes, s->chunk, MAX_SLICE_ITERS, st,
-                          s->d_out[k], s->d_opos[k], s->d_err, staged ? SERVER_STAGE_KIB : 0) != hipSuccess)
+                          KIND_LANES[kind], s->chunk, MAX_SLICE_ITERS, st, s->d_out[k], s->d_opos[k], s->d_err,
+                          KIND_STAGE[kind]) != hipSuccess)
         return false;
     // the launch's results, positions included, come back before its event
     if (hipMemcpyAsync(s->h_out[k], s->d_out[k], sizeof(pso::BatchResult) * n, hipMemcpyDeviceToHost, st) != hipSuccess ||
@@ -615,14 +632,17 @@ int pso_server_create(size_t mem_budget, int64_t chunk_updates, pso_server **out
         // resident at once: a swarm has at most half the co-resident
         // workgroups as parts, and a streamed launch takes half of them.  A
         // staged launch (one 1024-lane workgroup per compute unit, whatever
-        // its swarms) takes all of them (PSO_SERVER_GRID=half: half), so
+        // its swarms) and one that holds its parts in registers (four of 256
+        // lanes) take all of them (PSO_SERVER_GRID=half: half), so
         // while one launch drains, the other's workgroups take the compute
         // units it leaves (9.4k against 8.5k requests/s at 10 000/s).  Two
-        // staged launches cannot wait on each other: in a launch only the
+        // such launches cannot wait on each other: in a launch only the
         // swarm whose parts are being dequeued can wait on workgroups not yet
         // resident, and only while every resident workgroup of that launch
         // holds one of its parts; both launches stuck needs more parts in the
-        // two swarms than there are compute units, but each has at most half.
+        // two swarms than there are places, but each has at most half (of the
+        // compute units; parts held in registers go four to a unit, also
+        // beside the other kind).
         int capacity = 0;
         if (pso::batch_capacity(MAX_SERVER_D, pso::DEFAULT_BATCH_SHAPE.lanes, &capacity) != hipSuccess || capacity < 2) {
             server_free(s);
@@ -630,15 +650,17 @@ int pso_server_create(size_t mem_budget, int64_t chunk_updates, pso_server **out
         }
         const char *genv = getenv("PSO_SERVER_GRID");
         const int share = (genv && !strcmp(genv, "half")) ? STREAMS : 1;
-        s->grid_cap = capacity / STREAMS;
+        s->grid_cap[STREAMED] = s->launch_cap[STREAMED] = capacity / STREAMS;
         {
-            const char *env = getenv("PSO_SERVER_STAGED");
-            int cap_staged = 0;
-            if (!(env && !strcmp(env, "0")) &&
-                pso::batch_capacity(SERVER_STAGE_MAX_D, SERVER_STAGE_LANES, &cap_staged, SERVER_STAGE_KIB) == hipSuccess &&
-                cap_staged >= STREAMS) {
-                s->grid_cap_staged = cap_staged / STREAMS;
-                s->launch_cap_staged = cap_staged / share;
+            const char *env = getenv("PSO_SERVER_STAGED"), *reg = getenv("PSO_BATCH_REGISTERS");
+            for (int kind : {STAGED, REGISTERS}) {
+                int cap = 0;
+                if ((env && !strcmp(env, "0")) || (kind == REGISTERS && reg && !strcmp(reg, "0"))) continue;
+                if (pso::batch_capacity(SERVER_STAGE_MAX_D, KIND_LANES[kind], &cap, KIND_STAGE[kind]) != hipSuccess ||
+                    cap < STREAMS)
+                    continue;
+                s->grid_cap[kind] = cap / STREAMS;
+                s->launch_cap[kind] = cap / share;
             }
         }
         {
@@ -704,13 +726,31 @@ int pso_server_submit(pso_server *s, const pso_desc *d, uint64_t *ticket)
         if (d->shift) std::memcpy(r->shift.data(), d->shift, sizeof(float) * d->D);
         r->d.shift = nullptr;
         r->t_submit = s->now();
-        const uint32_t staged_parts =
-            s->grid_cap_staged > 0 && d->D <= SERVER_STAGE_MAX_D
-                ? pso::staged_parts((uint64_t)d->N, d->D, d->fitness_id, SERVER_STAGE_KIB, s->grid_cap_staged)
-                : 0;
-        r->staged = staged_parts > 0;
-        r->parts = r->staged ? staged_parts : pso::parts_for((uint64_t)d->N, d->D, s->grid_cap, pso::DEFAULT_BATCH_SHAPE);
-        const size_t bytes = pso::layout_of((uint64_t)d->N, d->D, false).total + pso::gang_bytes(r->parts, d->D);
+        float shift_max = 0.0f;
+        for (float v : r->shift) shift_max = std::max(shift_max, std::fabs(v));
+        const bool exact =
+            pso::short_forms_exact(d->fitness_id, d->bounds[0], d->bounds[1], d->c1, d->c2, shift_max, false);
+        const size_t state = pso::layout_of((uint64_t)d->N, d->D, false).total;
+        uint64_t in_flight = 0;
+        {
+            std::lock_guard<std::mutex> g(s->mu);
+            in_flight = s->submitted - s->completed - s->rejected - s->cancelled - s->timed_out;
+        }
+        uint32_t parts = 0;
+        for (int kind : {REGISTERS, STAGED}) {
+            if (parts > 0 || s->grid_cap[kind] < 1 || d->D > SERVER_STAGE_MAX_D || (kind == REGISTERS && !exact)) continue;
+            parts = pso::staged_parts((uint64_t)d->N, d->D, d->fitness_id, KIND_STAGE[kind], s->grid_cap[kind]);
+            // as if the requests in flight were like this one
+            if (kind == REGISTERS && s->grid_cap[STAGED] > 0 &&
+                !pso::registers_pay((uint64_t)d->N, d->D, parts, (in_flight + 1) * parts, s->launch_cap[kind]))
+                parts = 0;
+            // a registers request's gang region is the larger: where only it exceeds the budget, LDS
+            if (kind == REGISTERS && state + pso::resident_gang_bytes(parts, d->D) > s->budget) parts = 0;
+            if (parts > 0) r->kind = kind;
+        }
+        r->parts = parts > 0 ? parts : pso::parts_for((uint64_t)d->N, d->D, s->grid_cap[STREAMED], pso::DEFAULT_BATCH_SHAPE);
+        const size_t bytes =
+            state + (r->kind == REGISTERS ? pso::resident_gang_bytes : pso::gang_bytes)(r->parts, d->D);
         std::lock_guard<std::mutex> g(s->mu);
         // the request is listed before it is queued, and a failure to queue
         // it unlists it, so the scheduler never admits an unlisted ticket
