@@ -24,13 +24,20 @@
 // Deadlock freedom is the work queue's (the grid is co-resident, parts are
 // dequeued in order); every wait is bounded.
 //
-// Bound by vector instruction issue (60 % of the issue slots on the batch
-// below; the rest are the waits that four workgroups do not cover and the last
-// workgroups' tail).  256 swarms of 32 to 8192 particles, D = 2 to 64, 500
-// iterations: 30.4 ms LDS-staged, 19.7 ms here.  Four workgroups of 256 lanes
-// rather than one of 1024: the other three compute through one's meeting.
-// 16 dimensions per lane: 48 state registers of 121, and no shape of the range
-// needs more than four lanes per particle.
+// A part posts its candidate as soon as it has it and computes the own half of
+// the next iteration's Eq. 1 (Philox, w v + c1 r1 (p - x)) while the others
+// post; the wavefronts in that half yield issue slots to those in the other
+// one, on which some swarm's parts wait (s_setprio).
+//
+// Bound by vector instruction issue (62 instructions per update, 65 % of the
+// issue slots on the batch below) and by the slowest of a swarm's parts.  256
+// swarms of 32 to 8192 particles, D = 2 to 64, 500 iterations: 30.4 ms
+// LDS-staged; here 19.7 with the whole update between the meetings, 18.6 with
+// the own half ahead, 17.9 with its priority lowered.  Four workgroups of 256
+// lanes rather than one of 1024: the other three compute through one's
+// meeting.  16 dimensions per lane: 48 state registers of 128 (c2 r2 of the
+// own half waits in the lane's LDS terms), and no shape of the range needs more
+// than four lanes per particle.
 #include <algorithm>
 
 #include "pso_block.hpp"
@@ -109,9 +116,9 @@ __device__ __forceinline__ void resident_part(const BatchItem &item, const Batch
     const int d0 = k * cs, nd = k < L ? min(cs, D - d0) : 0;
     const bool valid = k < L && i < N, folder = valid && k == 0;
     float *s_g = lds, *s_shift = lds + RESIDENT_MAX_D;
-    float *s_t = s_shift + RESIDENT_MAX_D, *s_last = s_t + CW * (LANES - P);
+    float *s_t = s_shift + RESIDENT_MAX_D, *s_last = s_t + CW * LANES;
     uint32_t *s_imp = reinterpret_cast<uint32_t *>(s_last + (LANES - P));
-    float *my_t = s_t + (k > 0 ? (tid - P) * CW : 0u);
+    float *my_t = s_t + tid * CW;
 
     const bool started = uniform(res->started) != 0u;
     unsigned long long gkey = started ? uniform(res->gkey) : NO_KEY;
@@ -151,133 +158,164 @@ __device__ __forceinline__ void resident_part(const BatchItem &item, const Batch
     auto meets = [&]() { return tol > 0.0f && __builtin_fabsf(key_fitness(gkey) - fstar) < tol; };
     stop = stop || (started && meets());
     const unsigned long long c0 = wall_clock64();
-    // step 0 is Step 1 (Alg. 1), step t > 0 iteration t
-    while (!stop && t < t_end) {
+    // Step 0 is Step 1 (Alg. 1), step t > 0 iteration t.  A pass of the loop:
+    // the social half of Eq. 1, Eq. 2, the fitness, Steps 4 and 5's candidate
+    // and its posting (not on a resumed launch's first pass); the own half of
+    // the next step's Eq. 1, while the other parts post; the meeting.
+    // v holds its own half meanwhile, the first words of the lane's terms c2 r2
+    bool skip = started;
+    while (!stop) {
         const uint32_t step = (uint32_t)(t + 1);
-        const bool init = !started && step == 0u;
-        const uint32_t tag = init ? TAG_INIT : TAG_VEL;
-        Fitness<FIT> fit;
-        float zp = 0.0f;
+        unsigned long long comb = ~0ull;
+        bool mine = false, imp = false;
         int ndo = nd, ko = k;
         asm volatile("" : "+s"(ndo), "+s"(ko)); // scalar compares in the loop, not masks kept across it
+        if (!skip) {
+            const bool init = step == 0u;
+            Fitness<FIT> fit;
+            float zp = 0.0f;
 #pragma unroll
-        for (int q = 0; q < C; q += 2) {
-            if (q >= ndo) continue;
-            const U4 u = philox4x32_10(k0, k1, (uint32_t)(d0 + q) >> 1, i, step, tag);
-            float w0[2], w1[2] = {0.0f, 0.0f};
-            if (init) {
-                const float span = hi - lo, vspan = vmax + vmax;
+            for (int q = 0; q < C; q += 2) {
+                if (q >= ndo) continue;
+                float w0[2], w1[2] = {0.0f, 0.0f};
+                if (init) {
+                    const U4 u = philox4x32_10(k0, k1, (uint32_t)(d0 + q) >> 1, i, 0u, TAG_INIT);
+                    const float span = hi - lo, vspan = vmax + vmax;
 #pragma unroll
-                for (int h = 0; h < 2; ++h) {
-                    x[q + h] = clampf(lo + span * unit_float(word_r1(u, h)), lo, hi);
-                    v[q + h] = clampf(-vmax + vspan * unit_float(word_r2(u, h)), -vmax, vmax);
-                }
-            } else {
-#pragma unroll
-                for (int h = 0; h < 2; ++h) {
-                    const float r1 = (float)(word_r1(u, h) >> 8), r2 = (float)(word_r2(u, h) >> 8);
-                    const float own = (w * v[q + h]) + ((c1s * r1) * (p[q + h] - x[q + h]));
-                    const float nv = clamp_sym(own + ((c2s * r2) * (s_g[d0 + q + h] - x[q + h])), vmax);
-                    v[q + h] = nv;
-                    x[q + h] = clamp_pos(x[q + h] + nv, lo, hi);
-                }
-            }
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                const float z = x[q + h] - s_shift[d0 + q + h];
-                if constexpr (FIT == F_ROSENBROCK) {
-                    // a chunk's first term needs the previous chunk's z
-                    w0[h] = q + h == 0 ? z : rosen_term(z, zp);
+                    for (int h = 0; h < 2; ++h) {
+                        x[q + h] = clampf(lo + span * unit_float(word_r1(u, h)), lo, hi);
+                        v[q + h] = clampf(-vmax + vspan * unit_float(word_r2(u, h)), -vmax, vmax);
+                    }
                 } else {
-                    w0[h] = gang_term<FIT>(z);
-                    if constexpr (W == 2) w1[h] = cos2pi_small(z);
+#pragma unroll
+                    for (int h = 0; h < 2; ++h) {
+                        const float nv = clamp_sym(v[q + h] + (my_t[q + h] * (s_g[d0 + q + h] - x[q + h])), vmax);
+                        v[q + h] = nv;
+                        x[q + h] = clamp_pos(x[q + h] + nv, lo, hi);
+                    }
                 }
-                zp = z;
-            }
-            if (ko > 0) {
 #pragma unroll
                 for (int h = 0; h < 2; ++h) {
-                    my_t[q + h] = w0[h];
-                    if constexpr (W == 2) my_t[CP + q + h] = w1[h];
+                    const float z = x[q + h] - s_shift[d0 + q + h];
+                    if constexpr (FIT == F_ROSENBROCK) {
+                        // a chunk's first term needs the previous chunk's z
+                        w0[h] = q + h == 0 ? z : rosen_term(z, zp);
+                    } else {
+                        w0[h] = gang_term<FIT>(z);
+                        if constexpr (W == 2) w1[h] = cos2pi_small(z);
+                    }
+                    zp = z;
                 }
-            } else {
-                if (FIT != F_ROSENBROCK || q > 0) fit.acc = fit.acc + w0[0];
-                if constexpr (W == 2) fit.aux = fit.aux + w1[0];
-                if (q + 1 < ndo) {
-                    fit.acc = fit.acc + w0[1];
-                    if constexpr (W == 2) fit.aux = fit.aux + w1[1];
+                if (ko > 0) {
+#pragma unroll
+                    for (int h = 0; h < 2; ++h) {
+                        my_t[q + h] = w0[h];
+                        if constexpr (W == 2) my_t[CP + q + h] = w1[h];
+                    }
+                } else {
+                    if (FIT != F_ROSENBROCK || q > 0) fit.acc = fit.acc + w0[0];
+                    if constexpr (W == 2) fit.aux = fit.aux + w1[0];
+                    if (q + 1 < ndo) {
+                        fit.acc = fit.acc + w0[1];
+                        if constexpr (W == 2) fit.aux = fit.aux + w1[1];
+                    }
                 }
             }
-        }
-        if (L > 1) { // uniform
-            if (FIT == F_ROSENBROCK && k < L - 1) s_last[(uint32_t)k * P + j] = zp;
-            __syncthreads();
-            if (folder) {
-                for (int kk = 1; kk < L; ++kk) {
-                    const float *r = s_t + ((uint32_t)(kk - 1) * P + j) * CW;
-                    const int n = min(cs, D - kk * cs);
+            if (L > 1) { // uniform
+                if (FIT == F_ROSENBROCK && k < L - 1) s_last[(uint32_t)k * P + j] = zp;
+                __syncthreads();
+                if (folder) {
+                    for (int kk = 1; kk < L; ++kk) {
+                        const float *r = s_t + ((uint32_t)kk * P + j) * CW;
+                        const int n = min(cs, D - kk * cs);
 #pragma unroll
-                    for (int q0 = 0; q0 < C; q0 += 8) {
-                        if (q0 >= n) break;
-                        float b0[8], b1[8];
+                        for (int q0 = 0; q0 < C; q0 += 8) {
+                            if (q0 >= n) break;
+                            float b0[8], b1[8];
 #pragma unroll
-                        for (int q = 0; q < 8; ++q) {
-                            b0[q] = r[q0 + q];
-                            b1[q] = W == 2 ? r[CP + q0 + q] : 0.0f;
-                        }
-                        if (FIT == F_ROSENBROCK && q0 == 0) b0[0] = rosen_term(b0[0], s_last[(uint32_t)(kk - 1) * P + j]);
+                            for (int q = 0; q < 8; ++q) {
+                                b0[q] = r[q0 + q];
+                                b1[q] = W == 2 ? r[CP + q0 + q] : 0.0f;
+                            }
+                            if (FIT == F_ROSENBROCK && q0 == 0) b0[0] = rosen_term(b0[0], s_last[(uint32_t)(kk - 1) * P + j]);
 #pragma unroll
-                        for (int q = 0; q < 8; ++q) {
-                            if (q0 + q >= n) break;
-                            fit.acc = fit.acc + b0[q];
-                            if constexpr (W == 2) fit.aux = fit.aux + b1[q];
+                            for (int q = 0; q < 8; ++q) {
+                                if (q0 + q >= n) break;
+                                fit.acc = fit.acc + b0[q];
+                                if constexpr (W == 2) fit.aux = fit.aux + b1[q];
+                            }
                         }
                     }
                 }
             }
-        }
-        // Step 4 (strict; NaN never improves), or every particle at Step 1
-        const uint32_t slot = (uint32_t)((t + 1) % 3);
-        bool imp = false;
-        if (ko == 0) {
-            const float f = fit.value(D);
-            imp = (init && folder) || f < pf;
-            if (imp) {
-                pf = f;
-                const unsigned long long key = make_key(f, i);
-                if (key < gkey) atomicMin(&sh.comb[slot], (key >> 32 << 16) | j);
+            // Step 4 (strict; NaN never improves), or every particle at Step 1
+            const uint32_t slot = step % 3;
+            if (ko == 0) {
+                const float f = fit.value(D);
+                imp = (init && folder) || f < pf;
+                if (imp) {
+                    pf = f;
+                    const unsigned long long key = make_key(f, i);
+                    if (key < gkey) atomicMin(&sh.comb[slot], (key >> 32 << 16) | j);
+                }
+                if (L > 1 && k == 0) s_imp[j] = imp ? 1u : 0u;
             }
-            if (L > 1 && k == 0) s_imp[j] = imp ? 1u : 0u;
-        }
-        __syncthreads();
-        const unsigned long long comb = sh.comb[slot];
-        if (tid == 0) sh.comb[(slot + 2) % 3] = ~0ull; // the step after next's; its last readers passed the barrier
-        if (L > 1) imp = k < L && s_imp[j] != 0u;
-        if (init) imp = valid;
-        if (imp) {
+            __syncthreads();
+            comb = sh.comb[slot];
+            if (tid == 0) sh.comb[(slot + 2) % 3] = ~0ull; // the step after next's; its last readers passed the barrier
+            if (L > 1) imp = k < L && s_imp[j] != 0u;
+            if (init) imp = valid;
+            if (imp) {
 #pragma unroll
-            for (int q = 0; q < C; ++q) p[q] = x[q];
+                for (int q = 0; q < C; ++q) p[q] = x[q];
+            }
+            // Step 5: the part's candidate
+            mine = comb != ~0ull && valid && j == (uint32_t)(comb & 0xFFFFu);
+            if (parts > 1) {
+                const uint32_t seq = step + 1, par = seq & 1;
+                const unsigned long long ptag = (unsigned long long)seq << 32;
+                unsigned long long *const line = kw + ((size_t)par * parts + part) * RESIDENT_LINE;
+                if (mine) {
+                    unsigned long long *dst = pw + ((size_t)par * parts + part) * D + d0;
+#pragma unroll
+                    for (int q = 0; q < C; ++q)
+                        if (q < nd)
+                            __hip_atomic_store(&dst[q], ptag | __float_as_uint(x[q]), __ATOMIC_RELAXED,
+                                               __HIP_MEMORY_SCOPE_AGENT);
+                    if (k == 0) __hip_atomic_store(line + 1, ptag | i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                }
+                if (tid == 0)
+                    __hip_atomic_store(line, ((unsigned long long)(seq & 0xFFFFFFu) << 40) | (comb == ~0ull ? NONE40 : comb >> 16),
+                                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+            t = (long long)step;
         }
-        // Step 5
+        if (t < t_end) {
+            const uint32_t next = (uint32_t)(t + 1);
+            __builtin_amdgcn_s_setprio(0); // after the other workgroups' critical halves
+#pragma unroll
+            for (int q = 0; q < C; q += 2) {
+                if (q >= ndo) continue;
+                const U4 u = philox4x32_10(k0, k1, (uint32_t)(d0 + q) >> 1, i, next, TAG_VEL);
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    const float r1 = (float)(word_r1(u, h) >> 8), r2 = (float)(word_r2(u, h) >> 8);
+                    v[q + h] = (w * v[q + h]) + ((c1s * r1) * (p[q + h] - x[q + h]));
+                    my_t[q + h] = c2s * r2;
+                }
+            }
+        }
+        __builtin_amdgcn_s_setprio(3);
+        if (skip) {
+            skip = false;
+            if (t >= t_end) break;
+            continue;
+        }
+        // Step 5: the meeting
         unsigned long long win = comb == ~0ull ? ~0ull : comb >> 16 << 12;
         uint32_t win_idx = base + (uint32_t)(comb & 0xFFFFu);
-        const bool mine = comb != ~0ull && valid && j == (uint32_t)(comb & 0xFFFFu);
         if (parts > 1) {
             const uint32_t seq = step + 1, par = seq & 1;
-            const unsigned long long ptag = (unsigned long long)seq << 32;
-            unsigned long long *const line = kw + ((size_t)par * parts + part) * RESIDENT_LINE;
-            if (mine) {
-                unsigned long long *dst = pw + ((size_t)par * parts + part) * D + d0;
-#pragma unroll
-                for (int q = 0; q < C; ++q)
-                    if (q < nd)
-                        __hip_atomic_store(&dst[q], ptag | __float_as_uint(x[q]), __ATOMIC_RELAXED,
-                                           __HIP_MEMORY_SCOPE_AGENT);
-                if (k == 0) __hip_atomic_store(line + 1, ptag | i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            }
-            if (tid == 0)
-                __hip_atomic_store(line, ((unsigned long long)(seq & 0xFFFFFFu) << 40) | (comb == ~0ull ? NONE40 : comb >> 16),
-                                   __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             if (tid < 64) {
                 const unsigned long long w0 = wall_clock64();
                 unsigned long long best = ~0ull;
@@ -319,13 +357,12 @@ __device__ __forceinline__ void resident_part(const BatchItem &item, const Batch
             }
             __syncthreads();
         }
-        t = (long long)step;
         if (win != ~0ull) {
             gkey = (win >> 12 << 32) | win_idx;
             giter = t;
         }
         stop = meets();
-        if (sh.err) break; // uniform: written before the barrier; the host is told
+        if (sh.err || t >= t_end) break; // uniform: err was written before the barrier; the host is told
     }
     const unsigned long long ticks = wall_clock64() - c0;
     if (valid) {
@@ -399,7 +436,7 @@ k_batch_resident(const BatchItem *items, const BatchEntry *entries, BatchResult 
 
 // Gbest position and shift, the terms of the chunks after the first (two words
 // for Ackley), their last z and the improvement flags.
-size_t resident_lds() { return sizeof(float) * (2 * RESIDENT_MAX_D + (size_t)(LANES - 64) * (2 * CP + 1) + LANES); }
+size_t resident_lds() { return sizeof(float) * (2 * RESIDENT_MAX_D + (size_t)LANES * 2 * CP + (LANES - 64) + LANES); }
 
 hipError_t launch_batch_resident(const BatchItem *items, const BatchEntry *entries, BatchResult *results, uint32_t count,
                                  unsigned int *next, int grid, long long chunk, long long iter_cap, hipStream_t stream,
