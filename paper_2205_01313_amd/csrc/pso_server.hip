@@ -78,11 +78,12 @@ constexpr int STREAMS = PSO_SERVER_STREAMS;
 // launch), so a launch lasts about the slice whatever its mix, and a small
 // swarm is not held behind a large one's iterations.  A swarm's first
 // launch runs FIRST_ITERS iterations to measure it.  Measured on the
-// serving workload (p50 / p99 ms at 2000 and 10 000 requests/s): 300 us
-// 41 / 438 and 151 / 665; 1 ms 34 / 244 and 97 / 469; 2 ms 36 / 225 and
-// 91 / 434; 4 ms 39 / 224 and 92 / 375 (iteration-count chunks before:
-// 127 / 377 and 235 / 481).
-constexpr double SLICE_US_DEFAULT = 2000.0;
+// serving workload (p50 / p99 ms at 2000 and 10 000 requests/s, then
+// requests/s and p99 at 50 000): 500 us 4.6 / 9.2, 5.5 / 10.7, 20.2k, 590;
+// 1 ms 5.2 / 9.7, 6.4 / 11.2, 21.1k, 548; 2 ms 6.2 / 11.0, 7.8 / 13.0,
+// 21.7k, 526.  A burst of 200 requests: 4 ms 20.4 ms, 2 ms 18.2, 1 ms 17.7,
+// 500 us 17.9.
+constexpr double SLICE_US_DEFAULT = 1000.0;
 constexpr uint32_t FIRST_ITERS = 4;
 // Parts of one launch: at most this many per workgroup of its grid (a
 // launch's swarms are the longest-waiting ready ones).  Measured on the
