@@ -18,6 +18,7 @@
 #include "pso.h"
 #include "pso_block.hpp"
 #include "pso_gang.hpp"
+#include "pso_hold.hpp"
 #include "pso_guard.hpp"
 #include "pso_device.hpp"
 #include "pso_kernels.hpp"
@@ -385,10 +386,11 @@ int gang_run(pso_swarm *s, int64_t *left, bool *fetched)
     // a path forced from the environment is meant
     for (const char *name : {"PSO_STEP_SPLIT", "PSO_STEP_ONE", "PSO_SPLIT_PHASES", "PSO_RUN_GRAPH", "PSO_BLOCK_STAGED"})
         if (getenv(name)) return PSO_OK;
-    if (!pso::gang_accepts(s->fitness, s->args, s->shift_max, s->state_set) ||
-        !pso::gang_shape(s->fitness, s->args, *left, &sh))
-        return PSO_OK;
-    const size_t n = pso::gang_words(sh.G, s->D);
+    if (!pso::gang_accepts(s->fitness, s->args, s->shift_max, s->state_set)) return PSO_OK;
+    pso::HoldShape hs;
+    const bool hold = !pso::gang_shape(s->fitness, s->args, *left, &sh); // too large to be held whole
+    if (hold && !pso::hold_shape(s->fitness, s->args, *left, &hs)) return PSO_OK;
+    const size_t n = hold ? pso::hold_words(s->D) : pso::gang_words(sh.G, s->D);
     if (n > s->gang_words_n) {
         HIP_TRY(hipStreamSynchronize(s->stream));
         if (s->gang_words) (void)hipFree(s->gang_words);
@@ -405,7 +407,8 @@ int gang_run(pso_swarm *s, int64_t *left, bool *fetched)
     for (bool first = true; *left > 0; first = false) {
         const int64_t T = std::min(*left, most);
         if (!first) HIP_TRY(pso::launch_gang_arm(s->args, s->stream));
-        HIP_TRY(pso::launch_gang(s->args, sh, (uint32_t)T, s->gang_words, s->stream));
+        HIP_TRY(hold ? pso::launch_hold(s->args, hs, (uint32_t)T, s->gang_words, s->stream)
+                     : pso::launch_gang(s->args, sh, (uint32_t)T, s->gang_words, s->stream));
         int rc = fetch_ctrl(s, true);
         if (rc) return rc;
         if (s->host_ctrl->gang_state == pso::GANG_ABSENT) break;

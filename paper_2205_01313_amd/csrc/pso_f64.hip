@@ -28,6 +28,7 @@
 #include "pso_f64.hpp"
 #include "pso_f64_device.hpp"
 #include "pso_gang.hpp"
+#include "pso_hold.hpp"
 #include "pso_guard.hpp"
 #include "pso_kernels.hpp"
 
@@ -1244,14 +1245,18 @@ int gang_run64(pso_swarm64 *s, const char *path, int64_t *left, bool *absent)
         for (const char *name : {"PSO64_WIDE", "PSO64_SPLIT", "PSO64_BLOCK_STAGED"})
             if (getenv(name)) return PSO_OK;
     pso::Gang64Shape sh;
-    if (!pso::gang64_accepts(s->fitness, s->a) || !pso::gang64_shape(s->fitness, s->a, *left, &sh)) return PSO_OK;
+    if (!pso::gang64_accepts(s->fitness, s->a)) return PSO_OK;
+    pso::HoldShape hs;
+    const bool hold = !pso::gang64_shape(s->fitness, s->a, *left, &sh); // too large to be held whole
+    if (hold && (path || (getenv("PSO64_GANG_SHAPE") && !getenv("PSO_HOLD")) || !pso::hold_shape(s->fitness, s->a, *left, &hs))) return PSO_OK;
     const int64_t most =
         std::max<int64_t>(64, std::min<int64_t>(pso::GANG_MAX_T, int64_t(50000.0 / (1.5 + 1e-5 * double(s->N) * s->D))));
     for (bool first = true; *left > 0; first = false) {
         const int64_t T = std::min(*left, most);
         if (!first) HIP64_TRY(pso::launch64_gang_arm(s->a, s->stream));
-        HIP64_TRY(pso::launch_gang64(s->fitness, s->a, sh, (uint32_t)T, s->stream));
-        if (T == *left && sh.G == 1) {
+        HIP64_TRY(hold ? pso::launch_hold(s->a, hs, (uint32_t)T, s->stream)
+                       : pso::launch_gang64(s->fitness, s->a, sh, (uint32_t)T, s->stream));
+        if (!hold && T == *left && sh.G == 1) {
             *left = 0; // nothing to learn from the control block
             break;
         }

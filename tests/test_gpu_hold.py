@@ -1,0 +1,79 @@
+"""Runs that hold part of the state on the chip: sizes whose last lanes, parts
+and dimensions are ragged, forced below the size where they are chosen, bit for
+bit against the grid step (and the oracle), with continued runs, the state read
+and set in between, and the stop rule."""
+import numpy as np
+import pytest
+
+import paper_2205_01313_amd as pso
+from paper_2205_01313_amd import workloads as wl
+from tests.gpu_util import announce, assert_state_equal, gpu_swarm, oracle_swarm
+
+pytestmark = pytest.mark.gpu
+
+# N: one group per lane and several, lanes without one, a last group cut short;
+# D: fewer pairs than are held, some streamed, some in LDS, odd
+SIZES = [(70001, 3), (300001, 8), (524290, 12), (1100003, 5), (140003, 21), (131073, 26), (600001, 33), (70001, 47)]
+
+
+def runs(spec, cuts, tol=0.0):
+    with gpu_swarm(spec) as g:
+        for n in cuts:
+            r = g.run(n, tol=tol)
+        st = g.state()
+        hist = g.history(0, st["t"] + 1)
+        return r, st, hist, g.counters()["pbest_improvements"]
+
+
+@pytest.mark.parametrize("k", range(len(SIZES)))
+def test_held_runs_equal_the_grid_step(monkeypatch, k):
+    N, D = SIZES[k]
+    spec = wl.SwarmSpec(wl.FITNESS_NAMES[k % 5], N, D, 14, seed=77 + k, shift_amplitude=1.0)
+    announce(f"held run {spec.fitness} N={N} D={D}")
+    monkeypatch.setenv("PSO_GANG_SHAPE", "0,0")  # no gang of this shape
+    monkeypatch.setenv("PSO_HOLD", "1")          # whatever its share
+    r, st, hist, imp = runs(spec, (1, 4, 9))
+    monkeypatch.setenv("PSO_HOLD", "0")
+    r0, st0, hist0, imp0 = runs(spec, (14,))
+    assert r["gbest_fit"] == r0["gbest_fit"] and r["gbest_iter"] == r0["gbest_iter"] and imp == imp0
+    assert np.array_equal(hist, hist0)
+    for key in st0:
+        assert np.array_equal(np.asarray(st[key]), np.asarray(st0[key])), key
+    if N * D < 2_000_000:
+        assert_state_equal(st, oracle_swarm(spec, 16).run_f32(14), N, D)
+
+
+def test_held_run_stop_rule_and_default_choice(monkeypatch):
+    """The size at which a run holds part of its state by itself, stopped by
+    its rule at the iteration the grid step stops at."""
+    spec = wl.SwarmSpec("rastrigin", 1 << 19, 48, 40, seed=5, shift_amplitude=0.5)
+    announce("held run, stop rule")
+    with gpu_swarm(spec) as g:
+        f = g.run(20)["gbest_fit"]
+    out = []
+    for env in ("1", "0"):
+        monkeypatch.setenv("PSO_HOLD", env) if env == "0" else monkeypatch.delenv("PSO_HOLD", raising=False)
+        out.append(runs(spec, (40,), tol=float(f) * 1.0001))
+    assert out[0][1]["t"] == out[1][1]["t"] < 40
+    assert out[0][0]["gbest_fit"] == out[1][0]["gbest_fit"] and np.array_equal(out[0][2], out[1][2])
+
+
+@pytest.mark.parametrize("fit,N,D", [("sphere", 60001, 3), ("rastrigin", 131072, 32), ("ackley", 262145, 27),
+                                     ("rosenbrock", 70003, 40), ("cubic", 400001, 11)])
+def test_held_runs_in_binary64(monkeypatch, fit, N, D):
+    spec = wl.SwarmSpec(fit, N, D, 12, seed=N, shift_amplitude=1.0)
+    announce(f"held binary64 run {fit} N={N} D={D}")
+    out = []
+    monkeypatch.setenv("PSO64_GANG_SHAPE", "0,0")  # no gang of this shape
+    for hold in ("1", "0"):
+        monkeypatch.setenv("PSO_HOLD", hold)
+        with pso.Swarm64(fit, N, D, spec.box, spec.w, spec.c1, spec.c2, spec.vmax, 7,
+                         shift=np.asarray(spec.shift, np.float64)) as g:
+            for n in (1, 5, 6):
+                r = g.run(n)
+            st = g.state()
+            out.append((r, st))
+    (r, st), (r0, st0) = out
+    assert r["gbest_fit"] == r0["gbest_fit"] and r["gbest_iter"] == r0["gbest_iter"]
+    for key in st0:
+        assert np.array_equal(np.asarray(st[key]), np.asarray(st0[key])), key
