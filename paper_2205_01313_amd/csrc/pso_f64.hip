@@ -1249,6 +1249,7 @@ int gang_run64(pso_swarm64 *s, const char *path, int64_t *left, bool *absent)
     pso::HoldShape hs;
     const bool hold = !pso::gang64_shape(s->fitness, s->a, *left, &sh); // too large to be held whole
     if (hold && (path || (getenv("PSO64_GANG_SHAPE") && !getenv("PSO_HOLD")) || !pso::hold_shape(s->fitness, s->a, *left, &hs))) return PSO_OK;
+    bool ran = false;
     const int64_t most =
         std::max<int64_t>(64, std::min<int64_t>(pso::GANG_MAX_T, int64_t(50000.0 / (1.5 + 1e-5 * double(s->N) * s->D))));
     for (bool first = true; *left > 0; first = false) {
@@ -1269,7 +1270,10 @@ int gang_run64(pso_swarm64 *s, const char *path, int64_t *left, bool *absent)
             break;
         }
         *left = c.stop ? 0 : *left - T;
+        ran = true;
     }
+    // the narrow grid step takes no pending pbest position
+    if (hold && ran) HIP64_TRY(pso::launch64_flush(s->a, s->stream));
     return PSO_OK;
 }
 

@@ -61,6 +61,8 @@ def test_held_run_stop_rule_and_default_choice(monkeypatch):
 @pytest.mark.parametrize("fit,N,D", [("sphere", 60001, 3), ("rastrigin", 131072, 32), ("ackley", 262145, 27),
                                      ("rosenbrock", 70003, 40), ("cubic", 400001, 11)])
 def test_held_runs_in_binary64(monkeypatch, fit, N, D):
+    """Between the runs, steps of the wide and of the narrow grid step (which
+    takes no pending pbest position); the reference takes wide ones only."""
     spec = wl.SwarmSpec(fit, N, D, 12, seed=N, shift_amplitude=1.0)
     announce(f"held binary64 run {fit} N={N} D={D}")
     out = []
@@ -71,6 +73,10 @@ def test_held_runs_in_binary64(monkeypatch, fit, N, D):
                          shift=np.asarray(spec.shift, np.float64)) as g:
             for n in (1, 5, 6):
                 r = g.run(n)
+                if hold == "1":
+                    monkeypatch.setenv("PSO64_WIDE", str(n % 2))
+                g.step(2)
+                monkeypatch.delenv("PSO64_WIDE", raising=False)
             st = g.state()
             out.append((r, st))
     (r, st), (r0, st0) = out
