@@ -103,6 +103,8 @@ struct pso_swarm {
     int device = 0;
     Ctrl *host_ctrl = nullptr; // pinned mirror of the control block
     float *host_gpos = nullptr; // pinned, D floats
+    Ctrl *host_ctrl_dev = nullptr; // their device addresses (null: copied)
+    float *host_gpos_dev = nullptr;
     // RUN_GRAPH_STEPS step launches captured into a graph once (for the
     // variant and step path they were captured with) and replayed by pso_run
     hipGraph_t steps_graph = nullptr;
@@ -199,6 +201,12 @@ int create_common(int fitness_id, int64_t N, int32_t D, const float bounds[2], f
     if (hipHostMalloc(reinterpret_cast<void **>(&s->host_ctrl), sizeof(Ctrl), hipHostMallocDefault) != hipSuccess ||
         hipHostMalloc(reinterpret_cast<void **>(&s->host_gpos), sizeof(float) * D, hipHostMallocDefault) != hipSuccess)
         return cleanup(fail(PSO_ENOMEM, "pinned host allocation failed"));
+    if (D <= pso::FETCH_MAX_D &&
+        (hipHostGetDevicePointer(reinterpret_cast<void **>(&s->host_ctrl_dev), s->host_ctrl, 0) != hipSuccess ||
+         hipHostGetDevicePointer(reinterpret_cast<void **>(&s->host_gpos_dev), s->host_gpos, 0) != hipSuccess)) {
+        s->host_ctrl_dev = nullptr;
+        (void)hipGetLastError();
+    }
     s->args = pso::bind(s->ws, s->L, s->N, D);
     s->args.lo = bounds[0];
     s->args.hi = bounds[1];
@@ -222,8 +230,11 @@ int create_common(int fitness_id, int64_t N, int32_t D, const float bounds[2], f
 
 int fetch_ctrl(pso_swarm *s, bool with_gpos)
 {
-    HIP_TRY(hipMemcpyAsync(s->host_ctrl, s->args.ctrl, sizeof(Ctrl), hipMemcpyDeviceToHost, s->stream));
-    if (with_gpos)
+    if (s->host_ctrl_dev)
+        HIP_TRY(pso::launch_fetch(s->args, s->host_ctrl_dev, with_gpos ? s->host_gpos_dev : nullptr, s->stream));
+    else
+        HIP_TRY(hipMemcpyAsync(s->host_ctrl, s->args.ctrl, sizeof(Ctrl), hipMemcpyDeviceToHost, s->stream));
+    if (with_gpos && !s->host_ctrl_dev)
         HIP_TRY(hipMemcpyAsync(s->host_gpos, s->args.gpos, sizeof(float) * s->D, hipMemcpyDeviceToHost, s->stream));
     HIP_TRY(hipStreamSynchronize(s->stream));
     if (s->host_ctrl->err) return fail(PSO_EDEVICE, "device error bits 0x%x", s->host_ctrl->err);

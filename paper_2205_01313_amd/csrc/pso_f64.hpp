@@ -21,7 +21,8 @@ struct alignas(256) Ctrl64 {
     double tol, fstar;       // stop rule |gbest - fstar| < tol (tol <= 0: off)
     unsigned long long gang_arrive; // gang kernel: workgroup arrivals (monotonic within a launch)
     uint32_t gang_here, gang_state; // resident gang: parts at a launch's rendezvous, its outcome (GANG_GO, GANG_ABSENT)
-    unsigned char pad2[176];
+    long long run_t0;        // iterations completed when the current run was armed
+    unsigned char pad2[168];
 };
 static_assert(sizeof(Ctrl64) == 256, "Ctrl64 layout");
 
@@ -92,6 +93,14 @@ constexpr int GANG64_MAX_D_ALL = 512; // no instantiation holds more dimensions
 bool gang64_accepts(int fitness, const Swarm64Args &a);
 bool gang64_shape(int fitness, const Swarm64Args &a, int64_t T, Gang64Shape *out);
 size_t gang64_words(uint64_t N, int D); // 64-bit words reserved in the swarm's memory
+// What a run returns, as k_fetch64 writes it to pinned host memory; the gbest
+// position (D doubles) follows.
+struct Fetch64 {
+    Ctrl64 ctrl;
+    double value;
+    double pad[31];
+};
+hipError_t launch64_fetch(const Swarm64Args &a, Fetch64 *out, hipStream_t stream);
 hipError_t launch64_gang_arm(const Swarm64Args &a, hipStream_t stream);
 hipError_t launch_gang64(int fitness, const Swarm64Args &a, const Gang64Shape &s, uint32_t T, hipStream_t stream);
 

@@ -906,6 +906,25 @@ hipError_t launch_gang_arm(const SwarmArgs &a, hipStream_t stream)
     return hipGetLastError();
 }
 
+// The control block and, if asked for, the gbest position, written to pinned
+// host memory by one workgroup: one launch where the copies took two (a step of
+// Sphere D = 2, N = 1024 and its result: 28.2 -> 26.0 us).
+__global__ void __launch_bounds__(BLOCK) k_fetch(SwarmArgs a, Ctrl *ctrl, float *gpos)
+{
+    static_assert(sizeof(Ctrl) % sizeof(uint32_t) == 0, "copied in words");
+    const uint32_t *src = reinterpret_cast<const uint32_t *>(a.ctrl);
+    uint32_t *dst = reinterpret_cast<uint32_t *>(ctrl);
+    for (uint32_t w = threadIdx.x; w < sizeof(Ctrl) / sizeof(uint32_t); w += BLOCK) dst[w] = src[w];
+    if (!gpos) return;
+    for (int d = threadIdx.x; d < a.D; d += BLOCK) gpos[d] = a.gpos[d];
+}
+
+hipError_t launch_fetch(const SwarmArgs &a, Ctrl *ctrl, float *gpos, hipStream_t stream)
+{
+    hipLaunchKernelGGL(k_fetch, dim3(1), dim3(BLOCK), 0, stream, a, ctrl, gpos);
+    return hipGetLastError();
+}
+
 hipError_t launch_flush(const SwarmArgs &a, hipStream_t stream)
 {
     hipLaunchKernelGGL(k_flush, grid_all(a), dim3(BLOCK), 0, stream, a);
