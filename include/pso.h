@@ -136,7 +136,10 @@ int pso_step(pso_swarm *s);
  * registers and LDS (N*D up to about 8 million, D <= 512, N <= 262144) runs
  * as launches of up to 256 co-resident workgroups (about 50 ms each) that
  * keep it there and meet once per iteration, or once per block of iterations
- * while the gbest does not change.  If the workgroups are not resident
+ * while the gbest does not change; a larger one (N up to 4 million, D <= 512,
+ * max_iter >= 8) whose registers and LDS hold a tenth of it or more as such
+ * launches that keep that part there and stream the rest (PSO_HOLD=0 in the
+ * environment: not).  If the workgroups are not resident
  * together within 2 ms (another kernel holds the device) nothing has run and
  * the call goes on as below; a workgroup that is lost later (20 s) sets a
  * device error, returned as PSO_EDEVICE.  PSO_GANG=0 in the environment turns
@@ -223,7 +226,9 @@ int pso64_step(pso_swarm64 *s);
  * doubles), iteration of the last gbest change, iterations run.  A swarm
  * that fits the device's vector registers (N*D up to about 4 million, D <=
  * 256, N <= 262144) runs as launches of up to 256 co-resident workgroups as in
- * pso_run (not resident together within 2 ms: the paths below).  Else a swarm
+ * pso_run, a larger one (N up to 4 million, D <= 512, max_iter >= 3) as such
+ * launches that keep part of it there (not resident together within 2 ms: the
+ * paths below).  Else a swarm
  * with D >= 32 and N <= 32768 launches one grid step per iteration (lanes
  * share each particle's dimensions); else a swarm whose x, v, p and pbest
  * fitness fit one workgroup's LDS ((3D+1)*N doubles, up to about 160 KiB)

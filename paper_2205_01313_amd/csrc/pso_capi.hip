@@ -64,7 +64,8 @@ constexpr uint64_t MAX_BATCH_BYTES = uint64_t(1) << 52;
 // 5.2; Rastrigin D = 8, N = 2048: 13.7 / 10.7; D = 128, N = 512: 99.8 /
 // 14.0; Ackley D = 32, N = 1024: 26.2 / 9.8), so it runs only under
 // PSO_BLOCK_STAGED=0 (tests compare the two one-workgroup kernels).  The
-// resident gang takes every swarm it accepts before either (gang_run).
+// resident gang takes every swarm it accepts before either, and held runs
+// most larger ones (gang_run).
 #ifndef PSO_BLOCK_RUN_MAX_ND
 #define PSO_BLOCK_RUN_MAX_ND 65536
 #endif
@@ -382,8 +383,8 @@ int enqueue_steps(pso_swarm *s, int64_t n)
     return PSO_OK;
 }
 
-// Runs the swarm's next iterations as a resident gang where that suits it,
-// and takes what it ran off *left (the rest is for the other paths).  The
+// Runs the swarm's next iterations as a resident gang, or with part of the
+// state held on the chip (pso_hold.hip), where that suits it, and takes what it ran off *left (the rest is for the other paths).  The
 // stop rule is armed; *fetched: the host's copies of the control block and the
 // gbest position are those of the run's end.  A launch is kept to about
 // GANG_LAUNCH_US (an iteration takes at most about 1 us and 2.5 us per million

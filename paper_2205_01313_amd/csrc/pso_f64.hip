@@ -1224,7 +1224,8 @@ namespace {
     } while (0)
 
 // Paths of pso64_run.  The resident gang takes every swarm it accepts and
-// holds (pso_gang64.hip).  Of the others (Cubic, us per iteration): a swarm
+// holds (pso_gang64.hip), a held run the larger ones (pso_hold.hip).  Of the
+// others (Cubic, us per iteration): a swarm
 // that the split grid step takes (D >= 32, N <= 32768) runs one grid launch
 // per iteration (grid / one workgroup: N = 32, D = 120: 8.8 / 31.1; 192, 32:
 // 8.6 / 8.9); else a swarm whose state fits the LDS of one workgroup (x, v, p
@@ -1279,8 +1280,8 @@ int reinit64(pso_swarm64 *s)
     return PSO_OK;
 }
 
-// Runs the swarm's next iterations as a resident gang where that suits it,
-// and takes what it ran off *left; *absent: its parts were not resident
+// Runs the swarm's next iterations as a resident gang, or with part of the
+// state held on the chip (pso_hold.hip), where that suits it, and takes what it ran off *left; *absent: its parts were not resident
 // together, so no other gang is tried either; *fetched: it ran them all, and
 // *ctrl, *value and pos hold the results.  A launch is kept to about 50 ms
 // (an iteration takes at most about 1.5 us and 10 us per million
