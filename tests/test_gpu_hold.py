@@ -83,3 +83,37 @@ def test_held_runs_in_binary64(monkeypatch, fit, N, D):
     assert r["gbest_fit"] == r0["gbest_fit"] and r["gbest_iter"] == r0["gbest_iter"]
     for key in st0:
         assert np.array_equal(np.asarray(st[key]), np.asarray(st0[key])), key
+
+
+def test_held_runs_that_exclude_each_other():
+    """Two held runs at once need every compute unit each: one waits for the
+    other or takes the grid step, and both compute what they compute alone."""
+    import threading
+
+    specs = [wl.SwarmSpec("rastrigin", 1 << 19, 20, 60, seed=1, shift_amplitude=1.0),
+             wl.SwarmSpec("sphere", 600001, 16, 60, seed=2, shift_amplitude=1.0)]
+    announce("held runs at once")
+    alone = []
+    for sp in specs:
+        with gpu_swarm(sp) as g:
+            alone.append(g.run(sp.T))
+    swarms = [gpu_swarm(sp) for sp in specs]
+    out = [[], []]
+
+    def work(k):
+        for _ in range(4):
+            swarms[k].reset()
+            out[k].append(swarms[k].run(specs[k].T))
+
+    threads = [threading.Thread(target=work, args=(k,)) for k in range(2)]
+    for th in threads:
+        th.start()
+    for th in threads:
+        th.join()
+    for g in swarms:
+        g.close()
+    for k in range(2):
+        assert len(out[k]) == 4
+        for r in out[k]:
+            assert r["gbest_fit"] == alone[k]["gbest_fit"] and r["gbest_iter"] == alone[k]["gbest_iter"]
+            assert np.array_equal(r["gbest_pos"], alone[k]["gbest_pos"])
