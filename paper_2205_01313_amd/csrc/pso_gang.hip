@@ -208,6 +208,9 @@ __global__ void __launch_bounds__(MAXT) k_gang_resident(SwarmArgs a, GangArgs ga
         }
         if (folder) S.pf = a.pf[i];
     }
+    // every lane of a particle has read its mark before the folding lane clears
+    // it: a launch whose stop rule already holds meets no other barrier
+    if constexpr (MULTI) __syncthreads();
 
     float *s_g = s_gpos, *s_gn = s_gpos + DL; // in use, and the next one
     constexpr bool AHEAD = C <= 16 && PL == 0; // room for the next iteration's own half in registers

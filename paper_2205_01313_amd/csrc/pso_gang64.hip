@@ -179,6 +179,9 @@ __global__ void __launch_bounds__(MAXT) k_gang64_resident(Swarm64Args a, Gang64A
         }
         if (folder) S.pf = a.pf[i];
     }
+    // every lane of a particle has read its mark before the folding lane clears
+    // it: a launch whose stop rule already holds meets no other barrier
+    if constexpr (MULTI) __syncthreads();
 
     double *s_g = s_gpos, *s_gn = s_gpos + DL; // in use, and the next one
     constexpr bool AHEAD = C <= 8; // room for the next iteration's own half in registers

@@ -235,3 +235,26 @@ def test_gang_on_the_callers_stream():
             s = g.state()
             assert torch.equal(b, a @ a)
     assert_state_equal(s, oracle_swarm(spec, 8).run_f32(spec.T), spec.N, spec.D)
+
+
+@pytest.mark.parametrize("fit,N,D,shape", [("rastrigin", 200, 30, "8,64"), ("sphere", 4001, 12, "2,32"), ("rosenbrock", 150, 19, "4,152"),
+                                           ("ackley", 300, 66, "64,256")])
+def test_stopped_gang_keeps_the_pending_marks(monkeypatch, fit, N, D, shape):
+    """Steps leave pbest positions pending in x; a run whose stop rule already
+    holds runs no iteration and leaves the flushed state, in both precisions."""
+    spec = wl.SwarmSpec(fit, N, D, 4, seed=N + D, shift_amplitude=1.5)
+    announce(f"stopped gang {fit} N={N} D={D} shape {shape}")
+    c, p = shape.split(",")
+    monkeypatch.setenv("PSO_GANG_SHAPE", shape)
+    monkeypatch.setenv("PSO64_GANG_SHAPE", shape if int(c) <= 32 else "16,64")
+    for make, bits in ((gpu_swarm, np.uint32), (swarm64, np.uint64)):
+        out = []
+        for run in (False, True):
+            with make(spec) as g:
+                g.step(4)
+                if run:
+                    assert g.run(10, tol=1e30)["iters"] == 0
+                out.append(g.state())
+        assert out[0]["t"] == out[1]["t"] == 4
+        for k in ("x", "v", "p", "pf"):
+            assert np.array_equal(out[0][k].view(bits), out[1][k].view(bits)), k
