@@ -847,11 +847,12 @@ template <int FIT, int LANES>
 __global__ void __launch_bounds__(LANES) k_block_run_staged(SwarmArgs a, long long T)
 {
     __shared__ Scratch sc;
-    extern __shared__ float s_dyn[]; // gbest position, shift (D floats each, rounded up to 16 bytes), state
+    // gbest position, shift (D floats each, rounded up to 16 bytes), state (read in 16-byte vectors)
+    extern __shared__ __attribute__((aligned(16))) float s_staged[];
     Ctrl *c = a.ctrl;
     const int D = a.D;
     const int head = (D + 3) & ~3;
-    float *s_g = s_dyn, *s_shift = s_dyn + head, *s_state = s_dyn + 2 * head;
+    float *s_g = s_staged, *s_shift = s_staged + head, *s_state = s_staged + 2 * head;
     for (int d = threadIdx.x; d < D; d += LANES) {
         s_g[d] = a.gpos[d];
         s_shift[d] = a.shift[d];
@@ -929,8 +930,8 @@ __global__ void __launch_bounds__(LANES) k_batch_staged(const BatchItem *items, 
 {
     __shared__ Scratch sc;
     __shared__ uint32_t s_idx;
-    extern __shared__ float s_dyn[];
-    float *s_state = s_dyn + staged_head_floats(pos_stride);
+    extern __shared__ __attribute__((aligned(16))) float s_staged[];
+    float *s_state = s_staged + staged_head_floats(pos_stride);
     if (threadIdx.x == 0) sc.err = 0;
     for (;;) {
         if (threadIdx.x == 0) s_idx = atomicAdd(next, 1u);
@@ -940,7 +941,7 @@ __global__ void __launch_bounds__(LANES) k_batch_staged(const BatchItem *items, 
         if (j >= count) break; // uniform: every workgroup leaves once the list is drained
         const BatchEntry e = entries[j];
         const BatchItem &it = items[e.item];
-        float *s_g = s_dyn, *s_shift = s_dyn + ((pos_stride + 3) & ~3);
+        float *s_g = s_staged, *s_shift = s_staged + ((pos_stride + 3) & ~3);
         BatchResult *res = &results[e.item];
         switch (it.fitness) {
         case F_SPHERE: staged_part<F_SPHERE, LANES>(it, e.part, e.iters, res, chunk, iter_cap, s_g, s_shift, &sc, s_state, out_state, out_pos, e.out, pos_stride); break;

@@ -148,7 +148,7 @@ k_hold(typename R::Args a, HoldArgs<typename R::T> h)
     constexpr int VEC = R::VEC, WORDS = R::WORDS, HELD = held_of<T>(FIT);
     constexpr uint32_t ALL = (1u << VEC) - 1u;
     __shared__ HoldShared sh;
-    extern __shared__ char s_hold[];
+    extern __shared__ __attribute__((aligned(16))) char s_hold[]; // read in 16-byte vectors
     auto *c = a.ctrl;
     const int D = a.D, DP = (D + 1) / 2, M = h.lds_pairs;
     const uint32_t G = gridDim.x, part = blockIdx.x, tid = threadIdx.x, slots = h.slots;
