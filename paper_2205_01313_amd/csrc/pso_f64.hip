@@ -920,8 +920,10 @@ __global__ void __launch_bounds__(BLOCK64) k_fetch64(Swarm64Args a, Fetch64 *out
 
 hipError_t launch64_fetch(const Swarm64Args &a, Fetch64 *out, hipStream_t stream)
 {
-    hipLaunchKernelGGL(k_fetch64, dim3(1), dim3(BLOCK64), 0, stream, a, out);
-    return hipGetLastError();
+    // the launch's own status, not an earlier error of the thread's
+    Swarm64Args args = a;
+    void *params[] = {&args, &out};
+    return hipLaunchKernel(reinterpret_cast<const void *>(k_fetch64), dim3(1), dim3(BLOCK64), params, 0, stream);
 }
 
 // The resident gang's rendezvous fields before each of its launches after

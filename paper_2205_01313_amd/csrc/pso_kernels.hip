@@ -921,8 +921,11 @@ __global__ void __launch_bounds__(BLOCK) k_fetch(SwarmArgs a, Ctrl *ctrl, float 
 
 hipError_t launch_fetch(const SwarmArgs &a, Ctrl *ctrl, float *gpos, hipStream_t stream)
 {
-    hipLaunchKernelGGL(k_fetch, dim3(1), dim3(BLOCK), 0, stream, a, ctrl, gpos);
-    return hipGetLastError();
+    // the launch's own status: hipGetLastError would also return an earlier
+    // error of the thread's, and reading a result is no launch to its caller
+    SwarmArgs args = a;
+    void *params[] = {&args, &ctrl, &gpos};
+    return hipLaunchKernel(reinterpret_cast<const void *>(k_fetch), dim3(1), dim3(BLOCK), params, 0, stream);
 }
 
 hipError_t launch_flush(const SwarmArgs &a, hipStream_t stream)
