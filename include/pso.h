@@ -189,6 +189,12 @@ int pso_get_counters(pso_swarm *s, uint64_t *pbest_improvements);
  * stay 0 under the other variants.  Either pointer may be NULL. */
 int pso_get_async_counters(pso_swarm *s, uint64_t *tiles, uint64_t *fresh_tiles);
 
+/* Reads how many iterations the swarm's pso_run calls ran, since its creation,
+ * as co-resident workgroups that hold the whole swarm, as those that hold part
+ * of it, and on the other paths (pso_run; steps are not counted).  Each pointer
+ * may be NULL. */
+int pso_get_run_paths(pso_swarm *s, uint64_t *resident, uint64_t *held, uint64_t *other);
+
 /* Blocks until the swarm's enqueued work is done; reports device errors. */
 int pso_sync(pso_swarm *s);
 
@@ -237,6 +243,9 @@ int pso64_step(pso_swarm64 *s);
  * iteration.  Every path gives the same results. */
 int pso64_run(pso_swarm64 *s, int64_t max_iter, double tol, double f_star, double *gbest_value, double *gbest_pos,
               int64_t *gbest_iter, int64_t *iters_done);
+
+/* As pso_get_run_paths, of pso64_run. */
+int pso64_get_run_paths(pso_swarm64 *s, uint64_t *resident, uint64_t *held, uint64_t *other);
 
 /* Copies the state to host buffers (each may be NULL): x, v, p (D*N doubles
  * each, (d, i) at d*N + i), pbest fitness (N doubles), gbest particle index,
@@ -372,6 +381,9 @@ typedef struct pso_batch_shape {
 
 /* The batch's current shape (grid as launched: at most the entry count). */
 int pso_batch_get_shape(pso_batch *b, pso_batch_shape *shape);
+
+/* Whether the batch holds its parts in registers under its current shape. */
+int pso_batch_in_registers(pso_batch *b, int32_t *in_registers);
 
 /* Sets the shape for the following launches (synchronises the batch's
  * stream).  EINVAL for unsupported lanes, grid < 0, part_work < 1 (streamed),

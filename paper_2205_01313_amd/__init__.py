@@ -145,6 +145,16 @@ def pso_get_async_counters(h):
     return dict(tiles=n.value, fresh_tiles=f.value)
 
 
+def _run_paths(fn, h):
+    n = [ctypes.c_uint64() for _ in range(3)]
+    _check(getattr(lib(), fn)(h, *map(ctypes.byref, n)), fn)
+    return dict(resident=n[0].value, held=n[1].value, other=n[2].value)
+
+
+def pso_get_run_paths(h):
+    return _run_paths("pso_get_run_paths", h)
+
+
 def pso_sync(h):
     return _check(lib().pso_sync(h), "pso_sync")
 
@@ -214,6 +224,10 @@ class Swarm64:
         _check(lib().pso64_eval(self.h, pts.ctypes.data_as(dp), pts.shape[0], out.ctypes.data_as(dp)), "pso64_eval")
         return out
 
+    def run_paths(self):
+        """Iterations run() ran since creation: dict(resident, held, other)."""
+        return _run_paths("pso64_get_run_paths", self.h)
+
     def state(self):
         N, D = self.N, self.D
         out = dict(x=np.empty(D * N), v=np.empty(D * N), p=np.empty(D * N), pf=np.empty(N))
@@ -262,6 +276,13 @@ class Batch:
         sh = _native.PsoBatchShape()
         _check(lib().pso_batch_get_shape(self.h, ctypes.byref(sh)), "pso_batch_get_shape")
         return dict(lanes=sh.lanes, grid=sh.grid, part_work=sh.part_work, stage_kib=sh.stage_kib)
+
+    @property
+    def in_registers(self):
+        """Whether the parts are held in registers under the current shape."""
+        n = ctypes.c_int32()
+        _check(lib().pso_batch_in_registers(self.h, ctypes.byref(n)), "pso_batch_in_registers")
+        return bool(n.value)
 
     def set_shape(self, lanes, grid=0, part_work=1 << 17, stage_kib=0):
         """stage_kib > 0: each part's state in that many KiB of LDS for a
@@ -449,6 +470,10 @@ class Swarm:
 
     def counters(self):
         return pso_get_counters(self.h)
+
+    def run_paths(self):
+        """Iterations run() ran since creation: dict(resident, held, other)."""
+        return pso_get_run_paths(self.h)
 
     def async_counters(self):
         return pso_get_async_counters(self.h)

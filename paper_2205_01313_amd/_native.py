@@ -65,6 +65,7 @@ SIGNATURES = {
     "pso_set_state": (c_int, [c_vp, P(c_f), P(c_f), P(c_f), P(c_f), c_u64, P(c_f), c_i64, c_i64]),
     "pso_get_counters": (c_int, [c_vp, P(c_u64)]),
     "pso_get_async_counters": (c_int, [c_vp, P(c_u64), P(c_u64)]),
+    "pso_get_run_paths": (c_int, [c_vp, P(c_u64), P(c_u64), P(c_u64)]),
     "pso_sync": (c_int, [c_vp]),
     "pso_destroy": (c_int, [c_vp]),
     "pso_batch_create": (c_int, [P(PsoDesc), c_i64, c_vp, P(c_vp)]),
@@ -79,10 +80,12 @@ SIGNATURES = {
     "pso64_step": (c_int, [c_vp]),
     "pso64_run": (c_int, [c_vp, c_i64, c_f64, c_f64, P(c_f64), P(c_f64), P(c_i64), P(c_i64)]),
     "pso64_get_state": (c_int, [c_vp, P(c_f64), P(c_f64), P(c_f64), P(c_f64), P(c_i64), P(c_i64)]),
+    "pso64_get_run_paths": (c_int, [c_vp, P(c_u64), P(c_u64), P(c_u64)]),
     "pso64_eval": (c_int, [c_vp, P(c_f64), c_i64, P(c_f64)]),
     "pso64_destroy": (c_int, [c_vp]),
     "pso_set_max_lead": (c_int, [c_vp, c_i64]),
     "pso_batch_get_shape": (c_int, [c_vp, P(PsoBatchShape)]),
+    "pso_batch_in_registers": (c_int, [c_vp, P(c_i32)]),
     "pso_batch_set_shape": (c_int, [c_vp, P(PsoBatchShape)]),
     "pso_batch_autotune": (c_int, [c_vp, c_i64, P(PsoBatchShape)]),
     "pso_server_create": (c_int, [c_size, c_i64, P(c_vp)]),

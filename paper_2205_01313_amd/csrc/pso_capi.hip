@@ -116,6 +116,8 @@ struct pso_swarm {
     // the gang's meeting words (allocated at its first run)
     unsigned long long *gang_words = nullptr;
     size_t gang_words_n = 0;
+    // iterations that pso_run ran as a resident gang, held, and elsewhere
+    uint64_t ran_resident = 0, ran_held = 0, ran_other = 0;
 };
 
 namespace {
@@ -384,8 +386,8 @@ int enqueue_steps(pso_swarm *s, int64_t n)
 }
 
 // Runs the swarm's next iterations as a resident gang, or with part of the
-// state held on the chip (pso_hold.hip), where that suits it, and takes what it ran off *left (the rest is for the other paths).  The
-// stop rule is armed; *fetched: the host's copies of the control block and the
+// state held on the chip (pso_hold.hip), where that suits it, and takes what it
+// ran off *left (the rest is for the other paths).  The stop rule is armed; *fetched: the host's copies of the control block and the
 // gbest position are those of the run's end.  A launch is kept to about
 // GANG_LAUNCH_US (an iteration takes at most about 1 us and 2.5 us per million
 // particle-dimensions) so that other work on the device waits no longer for
@@ -416,6 +418,7 @@ int gang_run(pso_swarm *s, int64_t *left, bool *fetched)
         s->gang_words_n = n;
     }
     const int64_t most = std::max<int64_t>(64, std::min<int64_t>(pso::GANG_MAX_T, int64_t(GANG_LAUNCH_US / (1.0 + 2.5e-6 * double(s->N) * s->D))));
+    int64_t counted = 0;
     for (bool first = true; *left > 0; first = false) {
         const int64_t T = std::min(*left, most);
         if (!first) HIP_TRY(pso::launch_gang_arm(s->args, s->stream));
@@ -424,6 +427,9 @@ int gang_run(pso_swarm *s, int64_t *left, bool *fetched)
         int rc = fetch_ctrl(s, true);
         if (rc) return rc;
         if (s->host_ctrl->gang_state == pso::GANG_ABSENT) break;
+        const int64_t ran = s->host_ctrl->t - s->host_ctrl->t_run0;
+        (hold ? s->ran_held : s->ran_resident) += (uint64_t)(ran - counted);
+        counted = ran;
         *left -= T;
         if (s->host_ctrl->stop) *left = 0;
     }
@@ -463,6 +469,7 @@ int pso_run(pso_swarm *s, int64_t max_iter, float tol, float f_star, float *gbes
         if (max_iter < 0) return fail(PSO_EINVAL, "max_iter < 0");
         if (std::isnan(tol) || std::isnan(f_star)) return fail(PSO_EINVAL, "tol and f_star must not be NaN");
         HIP_TRY(pso::launch_arm(s->args, tol, f_star, s->stream));
+        const uint64_t on_chip = s->ran_resident + s->ran_held; // before this run
         bool fetched = false;
         if (s->variant == PSO_SYNC && max_iter > 0) {
             // the gang runs what it can; max_iter keeps what is left for the
@@ -535,6 +542,7 @@ int pso_run(pso_swarm *s, int64_t max_iter, float tol, float f_star, float *gbes
         if (gbest_pos_host) std::memcpy(gbest_pos_host, s->host_gpos, sizeof(float) * s->D);
         if (gbest_iter) *gbest_iter = c.giter;
         if (iters_done) *iters_done = c.t - c.t_run0;
+        s->ran_other += (uint64_t)(c.t - c.t_run0) - (s->ran_resident + s->ran_held - on_chip);
         return PSO_OK;
     });
 }
@@ -647,6 +655,17 @@ int pso_get_async_counters(pso_swarm *s, uint64_t *tiles, uint64_t *fresh_tiles)
         if (rc) return rc;
         if (tiles) *tiles = s->host_ctrl->tiles;
         if (fresh_tiles) *fresh_tiles = s->host_ctrl->fresh;
+        return PSO_OK;
+    });
+}
+
+int pso_get_run_paths(pso_swarm *s, uint64_t *resident, uint64_t *held, uint64_t *other)
+{
+    return pso::guarded([&]() -> int {
+        if (!s) return fail(PSO_EINVAL, "swarm is NULL");
+        if (resident) *resident = s->ran_resident;
+        if (held) *held = s->ran_held;
+        if (other) *other = s->ran_other;
         return PSO_OK;
     });
 }
@@ -1097,6 +1116,15 @@ int pso_batch_get_shape(pso_batch *b, pso_batch_shape *shape)
         shape->grid = b->grid;
         shape->part_work = b->shape.part_work;
         shape->stage_kib = b->shape.stage_kib;
+        return PSO_OK;
+    });
+}
+
+int pso_batch_in_registers(pso_batch *b, int32_t *in_registers)
+{
+    return pso::guarded([&]() -> int {
+        if (!b || !in_registers) return fail(PSO_EINVAL, "batch or in_registers is NULL");
+        *in_registers = b->grid_registers > 0;
         return PSO_OK;
     });
 }

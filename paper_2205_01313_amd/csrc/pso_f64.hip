@@ -1215,6 +1215,8 @@ struct pso_swarm64 {
     void *mem = nullptr;
     hipStream_t stream = nullptr;
     pso::Fetch64 *host = nullptr, *host_dev = nullptr; // pinned, D doubles behind it; its device address (null: copied)
+    // iterations that pso64_run ran as a resident gang, held, and elsewhere
+    uint64_t ran_resident = 0, ran_held = 0, ran_other = 0;
 };
 
 namespace {
@@ -1283,9 +1285,10 @@ int reinit64(pso_swarm64 *s)
 }
 
 // Runs the swarm's next iterations as a resident gang, or with part of the
-// state held on the chip (pso_hold.hip), where that suits it, and takes what it ran off *left; *absent: its parts were not resident
-// together, so no other gang is tried either; *fetched: it ran them all, and
-// *ctrl, *value and pos hold the results.  A launch is kept to about 50 ms
+// state held on the chip (pso_hold.hip), where that suits it, and takes what it
+// ran off *left; *absent: its parts were not resident together, so no other
+// gang is tried either; *fetched: it ran them all, and *ctrl, *value and pos
+// hold the results.  A launch is kept to about 50 ms
 // (an iteration takes at most about 1.5 us and 10 us per million
 // particle-dimensions) so that other work on the device waits no longer.
 int gang_run64(pso_swarm64 *s, const char *path, int64_t *left, bool *absent, pso::Ctrl64 *ctrl, double *value,
@@ -1304,7 +1307,7 @@ int gang_run64(pso_swarm64 *s, const char *path, int64_t *left, bool *absent, ps
     if (hold && (path || (getenv("PSO64_GANG_SHAPE") && !getenv("PSO_HOLD")) ||
                  !pso::hold_shape(s->fitness, s->a, *left, &hs)))
         return PSO_OK;
-    bool ran = false;
+    int64_t counted = 0;
     const int64_t most =
         std::max<int64_t>(64, std::min<int64_t>(pso::GANG_MAX_T, int64_t(50000.0 / (1.5 + 1e-5 * double(s->N) * s->D))));
     for (bool first = true; *left > 0; first = false) {
@@ -1312,10 +1315,6 @@ int gang_run64(pso_swarm64 *s, const char *path, int64_t *left, bool *absent, ps
         if (!first) HIP64_TRY(pso::launch64_gang_arm(s->a, s->stream));
         HIP64_TRY(hold ? pso::launch_hold(s->a, hs, (uint32_t)T, s->stream)
                        : pso::launch_gang64(s->fitness, s->a, sh, (uint32_t)T, s->stream));
-        if (!hold && T == *left && sh.G == 1) {
-            *left = 0; // nothing to learn from the control block
-            break;
-        }
         pso::Ctrl64 &c = *ctrl;
         if (int rc = fetch64(s, &c, value, pos)) return rc;
         if (c.err) return pso_internal_fail(PSO_EDEVICE, "a gang wait gave up (device error bits 0x%x)", c.err);
@@ -1323,12 +1322,14 @@ int gang_run64(pso_swarm64 *s, const char *path, int64_t *left, bool *absent, ps
             *absent = true;
             break;
         }
+        const int64_t ran = c.t - c.run_t0;
+        (hold ? s->ran_held : s->ran_resident) += (uint64_t)(ran - counted);
+        counted = ran;
         *left = c.stop ? 0 : *left - T;
         *fetched = *left == 0;
-        ran = true;
     }
     // the narrow grid step takes no pending pbest position
-    if (hold && ran) HIP64_TRY(pso::launch64_flush(s->a, s->stream));
+    if (hold && counted > 0) HIP64_TRY(pso::launch64_flush(s->a, s->stream));
     return PSO_OK;
 }
 
@@ -1450,6 +1451,7 @@ int pso64_run(pso_swarm64 *s, int64_t max_iter, double tol, double f_star, doubl
         pso::Ctrl64 c{};
         bool fetched = false; // the results, into c, gbest_value and gbest_pos
         HIP64_TRY(pso::launch64_arm(s->a, tol, f_star, s->stream));
+        const uint64_t on_chip = s->ran_resident + s->ran_held; // before this run
         const uint64_t nd = s->N * (uint64_t)s->D;
         const char *path = getenv("PSO64_PATH"); // tests of every path: block, gang, grid
         // the resident gang runs what it can; max_iter keeps what is left for
@@ -1491,6 +1493,18 @@ int pso64_run(pso_swarm64 *s, int64_t max_iter, double tol, double f_star, doubl
         if (c.err) return pso_internal_fail(PSO_EDEVICE, "a gang wait gave up (device error bits 0x%x)", c.err);
         if (gbest_iter) *gbest_iter = c.giter;
         if (iters_done) *iters_done = c.t - c.run_t0;
+        s->ran_other += (uint64_t)(c.t - c.run_t0) - (s->ran_resident + s->ran_held - on_chip);
+        return PSO_OK;
+    });
+}
+
+int pso64_get_run_paths(pso_swarm64 *s, uint64_t *resident, uint64_t *held, uint64_t *other)
+{
+    return pso::guarded([&]() -> int {
+        if (!s) return pso_internal_fail(PSO_EINVAL, "swarm is NULL");
+        if (resident) *resident = s->ran_resident;
+        if (held) *held = s->ran_held;
+        if (other) *other = s->ran_other;
         return PSO_OK;
     });
 }

@@ -1,0 +1,86 @@
+"""Which path ran: the shapes and sizes that the tests of the resident gang,
+the held runs and the register-held batches force or expect take that path (all
+paths compute the same bits, so those tests alone cannot tell)."""
+import pytest
+
+import paper_2205_01313_amd as pso
+from paper_2205_01313_amd import workloads as wl
+from tests import test_gpu_gang, test_gpu_hold, test_gpu_resident
+from tests.gpu_util import announce, gpu_swarm
+
+pytestmark = pytest.mark.gpu
+
+
+def cases_of(test, names):
+    """The values a test function is parametrised with."""
+    for mark in test.pytestmark:
+        if mark.name == "parametrize" and mark.args[0] == names:
+            return mark.args[1]
+    raise AssertionError(names)
+
+
+def paths_of(g, T):
+    g.run(T)
+    n = g.run_paths()
+    assert sum(n.values()) == T
+    return n
+
+
+def test_forced_gang_shapes_run_resident(monkeypatch):
+    announce("forced gang shapes")
+    for fit, N, D, shape in cases_of(test_gpu_gang.test_gang_shapes_equal_oracle, "fit,N,D,shape"):
+        monkeypatch.setenv("PSO_GANG_SHAPE", shape)
+        with gpu_swarm(wl.SwarmSpec(fit, N, D, 20, seed=N)) as g:
+            assert paths_of(g, 20)["resident"] == 20, (fit, N, D, shape)
+
+
+def test_forced_binary64_gang_shapes_run_resident(monkeypatch):
+    announce("forced binary64 gang shapes")
+    forced = [(f, *c) for c in cases_of(test_gpu_gang.test_gang64_transcendental_equals_grid_steps, "N,D,shape")
+              for f in ("rastrigin", "ackley")]
+    forced += cases_of(test_gpu_gang.test_gang64_shapes_equal_oracle, "fit,N,D,shape")
+    for fit, N, D, shape in forced:
+        monkeypatch.setenv("PSO64_GANG_SHAPE", shape)
+        with test_gpu_gang.swarm64(wl.SwarmSpec(fit, N, D, 20, seed=N)) as g:
+            assert paths_of(g, 20)["resident"] == 20, (fit, N, D, shape)
+
+
+def test_chosen_gangs_run_resident():
+    """The sizes of the tests that leave the choice to the rule."""
+    announce("chosen gangs")
+    for name, make in (("test_gang_blocks_and_stop_rule", gpu_swarm), ("test_gang64_blocks_and_stop_rule", test_gpu_gang.swarm64)):
+        for fit, N, D, _ in cases_of(getattr(test_gpu_gang, name), "fit,N,D,tol"):
+            with make(wl.SwarmSpec(fit, N, D, 100, seed=N)) as g:
+                assert paths_of(g, 100)["resident"] == 100, (fit, N, D)
+
+
+def test_held_runs_are_held(monkeypatch):
+    announce("held runs")
+    with gpu_swarm(wl.SwarmSpec("rastrigin", 1 << 19, 48, 40, seed=5)) as g: # chosen by the rule
+        assert paths_of(g, 20)["held"] == 20
+    monkeypatch.setenv("PSO_HOLD", "1")
+    monkeypatch.setenv("PSO_GANG_SHAPE", "0,0")
+    for k, (N, D) in enumerate(test_gpu_hold.SIZES):
+        with gpu_swarm(wl.SwarmSpec(wl.FITNESS_NAMES[k % 5], N, D, 5, seed=k)) as g:
+            assert paths_of(g, 5)["held"] == 5, (N, D)
+    monkeypatch.setenv("PSO64_GANG_SHAPE", "0,0")
+    for fit, N, D in cases_of(test_gpu_hold.test_held_runs_in_binary64, "fit,N,D"):
+        sp = wl.SwarmSpec(fit, N, D, 5, seed=N)
+        with pso.Swarm64(fit, N, D, sp.box, sp.w, sp.c1, sp.c2, sp.vmax, 7) as g:
+            assert paths_of(g, 5)["held"] == 5, (fit, N, D)
+
+
+def test_switched_off_paths_do_not_run(monkeypatch):
+    announce("paths switched off")
+    monkeypatch.setenv("PSO_GANG", "0")
+    with gpu_swarm(wl.SwarmSpec("sphere", 3000, 12, 30, seed=1)) as g:
+        assert paths_of(g, 30) == dict(resident=0, held=0, other=30)
+
+
+@pytest.mark.parametrize("name", list(test_gpu_resident.EDGES))
+def test_batches_of_the_edges_are_held_in_registers(name):
+    announce(f"register-held batch: {name}")
+    with pso.Batch(test_gpu_resident.specs_of(name)) as b:
+        assert b.in_registers
+        b.set_shape(256, 0, 1 << 17)
+        assert not b.in_registers
