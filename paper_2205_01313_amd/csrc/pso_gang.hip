@@ -100,6 +100,25 @@ __device__ __forceinline__ void own_half(const SwarmArgs &a, const GangArgs &ga,
     }
 }
 
+// The least of a wavefront's candidates into *least, called by the lanes that
+// have one.  A swarm on its way down has many at once, and atomics of one
+// address take their turns (Cubic D = 32, N = 64, whose particles improve
+// together: 50 iterations 218 us, 155 with one atomic a wavefront).  A candidate
+// that beats the one in hand takes its place until none does: fewer rounds than
+// a butterfly has for the few there are, and nothing where there is none.
+__device__ __forceinline__ void post_least(unsigned long long *least, unsigned long long comb)
+{
+    const uint32_t lo = (uint32_t)comb, hi = (uint32_t)(comb >> 32);
+    unsigned long long best = ((unsigned long long)(uint32_t)__builtin_amdgcn_readfirstlane((int)hi) << 32) |
+                              (uint32_t)__builtin_amdgcn_readfirstlane((int)lo);
+    while (const unsigned long long m = __ballot(comb < best)) {
+        const int l = __builtin_ctzll(m);
+        best = ((unsigned long long)(uint32_t)__builtin_amdgcn_readlane((int)hi, l) << 32) |
+               (uint32_t)__builtin_amdgcn_readlane((int)lo, l);
+    }
+    if (comb == best) atomicMin(least, best); // one lane: particles differ
+}
+
 struct GangShared {
     unsigned long long comb[3]; // a block's best candidate: j << 48 | order bits << 16 | particle of the part
     unsigned long long win;     // the meeting's result: low 40 bits of the winner's word << 8 | part, NO_COMB if none
@@ -376,8 +395,7 @@ __global__ void __launch_bounds__(MAXT) k_gang_resident(SwarmArgs a, GangArgs ga
         }
         if constexpr (MULTI) {
             if (k == FK && j < P) s_imp[j] = imp ? 1u : 0u;
-            if (collect && cand)
-                atomicMin(&sh.comb[slot], (1ull << 48) | ((unsigned long long)ord << 16) | j);
+            if (collect && cand) post_least(&sh.comb[slot], (1ull << 48) | ((unsigned long long)ord << 16) | j);
             __syncthreads();
             imp = j < P && s_imp[j] != 0u;
         }
@@ -424,8 +442,7 @@ __global__ void __launch_bounds__(MAXT) k_gang_resident(SwarmArgs a, GangArgs ga
                 iterate(tb + (uint32_t)ran, slot, false, cand, ord);
                 any = __any(cand);
             } while (ran < n && !any);
-            if (cand)
-                atomicMin(&sh.comb[slot], ((unsigned long long)ran << 48) | ((unsigned long long)ord << 16) | j);
+            if (cand) post_least(&sh.comb[slot], ((unsigned long long)ran << 48) | ((unsigned long long)ord << 16) | j);
             __syncthreads();
             comb = sh.comb[slot];
         }
@@ -707,11 +724,12 @@ static size_t gang_lds(int fitness, int D, const GangKernel &kn, uint32_t P, uin
     return sizeof(float) * f;
 }
 
-// One shape's kernel, lanes and LDS, or false if no instantiation holds it.
-static bool gang_layout(int fitness, const SwarmArgs &a, int C, uint32_t P, GangShape *out)
+// One shape's kernel, lanes and LDS on a device of cus compute units and lds_max
+// bytes of LDS (asked for once a choice, which tries up to forty shapes), or
+// false if no instantiation holds it.
+static bool gang_layout(int fitness, const SwarmArgs &a, int cus, int lds_max, int C, uint32_t P, GangShape *out)
 {
-    int cus = 0, lds_max = 0, nk = 0;
-    if (!gang_device(&cus, &lds_max)) return false;
+    int nk = 0;
     const GangKernel *tab = gang_kernels(fitness, &nk);
     const uint32_t L = ((uint32_t)a.D + C - 1) / C;
     const uint64_t lanes = ((uint64_t)P * L + 63) / 64 * 64, G = ((uint64_t)a.N + P - 1) / P;
@@ -759,16 +777,18 @@ static bool gang_layout(int fitness, const SwarmArgs &a, int C, uint32_t P, Gang
 //     39.2; N = 262144: D = 16 8.3 / 25.2, D = 30 C = 32 16.2 / 37.9
 bool gang_shape(int fitness, const SwarmArgs &a, int64_t T, GangShape *out)
 {
+    int cus = 0, lds_max = 0;
+    if (!gang_device(&cus, &lds_max)) return false;
+    auto layout = [&](int c, uint32_t P, GangShape *s) { return gang_layout(fitness, a, cus, lds_max, c, P, s); };
     if (const char *env = getenv("PSO_GANG_SHAPE")) { // "C,P": forced (tests, measurements)
         int c = 0, p = 0;
         return sscanf(env, "%d,%d", &c, &p) == 2 && c >= 1 && p >= 16 && p <= 1024 &&
-               gang_layout(fitness, a, c, (uint32_t)p, out);
+               layout(c, (uint32_t)p, out);
     }
     const int D = a.D;
     const uint32_t N = a.N;
     if (N < 32 && D > 24 && D <= 110) return false;
-    if (one_part(N, D, T, 256, [&](int c, uint32_t P) { return gang_layout(fitness, a, c, P, out); }))
-        return true;
+    if (one_part(N, D, T, 256, [&](int c, uint32_t P) { return layout(c, P, out); })) return true;
     int c = D == 1 ? 1 : 2;
     uint32_t pmin = 256;
     if (D > 64) c = 8, pmin = 16;
@@ -781,11 +801,11 @@ bool gang_shape(int fitness, const SwarmArgs &a, int64_t T, GangShape *out)
         uint32_t P = c >= 16 ? std::max(pmin, 64u) : pmin;
         if (L == 1) P = std::max(P, 64u);
         GangShape s;
-        bool ok = gang_layout(fitness, a, c, P, &s);
+        bool ok = layout(c, P, &s);
         // more particles of a part while there are too many parts
         while (P < 1024 && (a.N + P - 1) / P > (D <= 2 ? 256u : 128u)) {
             P *= 2;
-            const bool more = gang_layout(fitness, a, c, P, &s);
+            const bool more = layout(c, P, &s);
             if (ok && !more) break;
             ok = more;
         }

@@ -656,10 +656,9 @@ size_t gang64_words(uint64_t N, int D)
     return parts < 2 ? 0 : (size_t)(2 * parts * KEY_STRIDE + 2 * parts * 2 * (uint64_t)D);
 }
 
-static bool gang64_layout(int fitness, const Swarm64Args &a, int C, uint32_t P, Gang64Shape *out)
+static bool gang64_layout(int fitness, const Swarm64Args &a, int cus, int lds_max, int C, uint32_t P, Gang64Shape *out)
 {
-    int cus = 0, lds_max = 0, nk = 0;
-    if (!gang_device(&cus, &lds_max)) return false;
+    int nk = 0;
     const Gang64Kernel *tab = gang64_kernels(fitness, &nk);
     const uint32_t L = ((uint32_t)a.D + C - 1) / C;
     const uint64_t lanes = ((uint64_t)P * L + 63) / 64 * 64, G = ((uint64_t)a.N + P - 1) / P;
@@ -695,22 +694,25 @@ static bool gang64_layout(int fitness, const Swarm64Args &a, int C, uint32_t P, 
 // 8, which spills) / 40.8.
 bool gang64_shape(int fitness, const Swarm64Args &a, int64_t T, Gang64Shape *out)
 {
+    int cus = 0, lds_max = 0;
+    if (!gang_device(&cus, &lds_max)) return false;
+    auto layout = [&](int c, uint32_t P, Gang64Shape *s) { return gang64_layout(fitness, a, cus, lds_max, c, P, s); };
     if (const char *env = getenv("PSO64_GANG_SHAPE")) { // "C,P": forced (tests, measurements)
         int c = 0, p = 0;
         return sscanf(env, "%d,%d", &c, &p) == 2 && c >= 1 && p >= 16 && p <= 1024 &&
-               gang64_layout(fitness, a, c, (uint32_t)p, out);
+               layout(c, (uint32_t)p, out);
     }
     const int D = a.D;
     const uint32_t N = a.N;
     // double cos and exp: lanes of few dimensions, in several parts sooner
     const bool heavy = fitness == F_RASTRIGIN || fitness == F_ACKLEY;
     if (one_part(N, D, T, 0, [&](int c, uint32_t P) {
-            return !(heavy && D > 2 && c > 2) && gang64_layout(fitness, a, c, P, out);
+            return !(heavy && D > 2 && c > 2) && layout(c, P, out);
         }))
         return true;
     if (heavy && D > 12 && D <= 64) { // one_part starts with larger chunks there
         const uint32_t packed = std::max(16u, (N + 3) / 4 * 4);
-        if (packed * ((uint32_t)(D + 1) / 2) <= 1024 && gang64_layout(fitness, a, 2, packed, out)) return true;
+        if (packed * ((uint32_t)(D + 1) / 2) <= 1024 && layout(2, packed, out)) return true;
     }
     int c = D == 1 ? 1 : 2;
     uint32_t pmin = 256, parts = 128;
@@ -725,11 +727,11 @@ bool gang64_shape(int fitness, const Swarm64Args &a, int64_t T, Gang64Shape *out
         uint32_t P = c >= 16 ? std::max(pmin, 64u) : pmin;
         if (L == 1) P = std::max(P, 64u);
         Gang64Shape s;
-        bool ok = gang64_layout(fitness, a, c, P, &s);
+        bool ok = layout(c, P, &s);
         // more particles of a part while there are too many parts
         while (P < 1024 && (a.N + P - 1) / P > parts) {
             P *= 2;
-            const bool more = gang64_layout(fitness, a, c, P, &s);
+            const bool more = layout(c, P, &s);
             if (ok && !more) break;
             ok = more;
         }
