@@ -788,7 +788,29 @@ bool gang_shape(int fitness, const SwarmArgs &a, int64_t T, GangShape *out)
     const int D = a.D;
     const uint32_t N = a.N;
     if (N < 32 && D > 24 && D <= 110) return false;
-    if (one_part(N, D, T, 256, [&](int c, uint32_t P) { return layout(c, P, out); })) return true;
+    // Where the gbest changes in most iterations, no block of them pays for what
+    // surrounds it, and the one-workgroup run is faster (us of a run, here / there:
+    // Sphere D = 2, T = 300: N = 641 445 / 331, 1024 475 / 375; N = 1500 T = 100
+    // 223 / 185; Ackley N = 600, D = 2, T = 100 207 / 182, N = 800, D = 1 195 / 175);
+    // at T = 600 the two are level, and Rastrigin and Cubic settle too early.
+    const bool late = settles_late(fitness);
+    if (late && D == 2 && N > 640 && N <= 1600 && T < (N <= 1300 ? 500 : 300)) return false;
+    if (fitness == F_ACKLEY && D <= 2 && N > 384 && N <= 1024 && T < 200) return false;
+    // A brief run stays in one part longer (settles_late; us of 200 iterations, one
+    // part / more: Rosenbrock D = 3, N = 800 400 / 490; Rastrigin D = 2, N = 641
+    // 203 / 196, of 100 137 / 146; Sphere D = 2, N = 641 of 600 621 / 697).
+    const bool brief = T < 200, longer = late && T < 800;
+    const uint32_t most2 = brief ? 1024 : longer && D == 2 ? 768 : 640, most4 = brief || longer ? 960 : 768;
+    if (one_part(N, D, most2, most4, 256, [&](int c, uint32_t P) { return layout(c, P, out); })) return true;
+    // Several parts: the state's way in and out of the registers and the
+    // rendezvous of up to 256 parts have to pay.  Against the step launches (us of
+    // a run of T, here / there): N = 4000, D = 30 T = 1 35 / 29, 2 39 / 39; N =
+    // 131072: D = 2 T = 1 59 / 26, 4 65 / 49, 8 70 / 74; D = 16 T = 2 63 / 50, 4 66 /
+    // 78; D = 30 T = 1 80 / 51, 2 84 / 92; N = 262144: D = 1 T = 4 90 / 56, 8 100 / 93;
+    // D = 8 T = 4 102 / 79, 6 110 / 106; D = 30 T = 2 129 / 95, 4 155 / 165.  Up to
+    // N = 65536 one iteration of D <= 16 is level with the steps.
+    const int64_t shortest = N <= 65536 ? (D > 16 ? 2 : 1) : D <= 4 ? 8 : D <= 16 ? (N > 131072 ? 6 : 4) : (N > 131072 ? 4 : 2);
+    if (T < shortest) return false;
     int c = D == 1 ? 1 : 2;
     uint32_t pmin = 256;
     if (D > 64) c = 8, pmin = 16;

@@ -69,19 +69,20 @@ bool gang_accepts(int fitness, const SwarmArgs &a, float shift_max, bool state_s
 bool gang_shape(int fitness, const SwarmArgs &a, int64_t T, GangShape *out);
 // 64-bit device words of the meeting.
 size_t gang_words(uint32_t parts, int D);
+// Sphere and Rosenbrock go down one valley and improve their gbest in most of
+// the first 500 to 1000 iterations, where the others settle after 100 to 200.
+// Every change is a meeting, so while it lasts fewer parts are better.
+inline bool settles_late(int fitness) { return fitness == 0 || fitness == 2; }
 // A swarm small enough for one part: layout(C, P) with its particles packed
 // (whole wavefronts where a lane holds a particle) and the smallest chunk that
-// fits, from C = 4 on for D > 12, whose fold is shorter that way.  A brief run
-// spends its iterations where the gbest still changes often and every change
-// is a meeting, so it stays in one part longer (Sphere D = 2, N = 818, one part
-// / four: 1.81 / 2.17 us per iteration of 60, 1.22 / 1.27 of 300).
+// fits, from C = 4 on for D > 12, whose fold is shorter that way.  most2, most4
+// and most8: the most particles of one part at D <= 2, at D <= 4 and at C = 8.
 template <class F>
-inline bool one_part(uint32_t N, int D, int64_t T, uint32_t most8, F &&layout)
+inline bool one_part(uint32_t N, int D, uint32_t most2, uint32_t most4, uint32_t most8, F &&layout)
 {
     const uint32_t whole = (N + 63) / 64 * 64, packed = std::max(16u, (N + 3) / 4 * 4);
-    const bool brief = T < 200;
-    if (D <= 2) return N <= (brief ? 1024u : 640u) && layout(D, whole);
-    if (D <= 4) return N <= 512 ? layout(2, packed) : N <= (brief ? 960u : 768u) && layout(4, whole);
+    if (D <= 2) return N <= most2 && layout(D, whole);
+    if (D <= 4) return N <= 512 ? layout(2, packed) : N <= most4 && layout(4, whole);
     for (int c = D <= 12 ? 2 : 4; c <= 8; c *= 2) {
         const uint32_t L = ((uint32_t)D + c - 1) / c;
         if (c == 8 && (N > most8 || (uint64_t)N * D > 6500)) return false;

@@ -706,7 +706,15 @@ bool gang64_shape(int fitness, const Swarm64Args &a, int64_t T, Gang64Shape *out
     const uint32_t N = a.N;
     // double cos and exp: lanes of few dimensions, in several parts sooner
     const bool heavy = fitness == F_RASTRIGIN || fitness == F_ACKLEY;
-    if (one_part(N, D, T, 0, [&](int c, uint32_t P) {
+    // Sphere and Rosenbrock improve their gbest for long (settles_late) and stay in
+    // one part (us of 1000 iterations, one part / more / the paths below: Sphere
+    // D = 2, N = 641 1535 / 1797 / 1694, N = 1024 1789 / 1774 / 1932; Rosenbrock D = 3,
+    // N = 800 2490 / 2953 / 2648); Rastrigin and Ackley leave it at once, a brief run
+    // of Cubic stays (of 100 iterations, Ackley N = 900, D = 1 339 / 269 / 329).
+    const bool late = settles_late(fitness), brief = T < 200;
+    const uint32_t most2 = heavy ? 640 : brief ? 1024 : late && D == 2 ? 768 : 640;
+    const uint32_t most4 = late ? 1024 : brief ? 960 : 768;
+    if (one_part(N, D, most2, most4, 0, [&](int c, uint32_t P) {
             return !(heavy && D > 2 && c > 2) && layout(c, P, out);
         }))
         return true;

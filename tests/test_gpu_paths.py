@@ -84,3 +84,23 @@ def test_batches_of_the_edges_are_held_in_registers(name):
         assert b.in_registers
         b.set_shape(256, 0, 1 << 17)
         assert not b.in_registers
+
+
+# T of the runs that stay off the resident gang, and the first T on it
+@pytest.mark.parametrize("fit,N,D,off,on", [
+    ("sphere", 262144, 8, (1, 2, 4), 6), ("sphere", 131072, 2, (1, 4), 8), ("ackley", 131072, 30, (1,), 2),
+    ("rastrigin", 262144, 30, (1, 2), 4), ("rosenbrock", 4000, 30, (1,), 2), ("cubic", 16384, 2, (), 1),
+    ("sphere", 641, 2, (60, 200, 400), 500), ("rosenbrock", 1300, 2, (50, 300), 500), ("sphere", 640, 2, (), 200),
+    ("ackley", 600, 2, (50, 199), 200), ("ackley", 900, 1, (50, 100), 200), ("rastrigin", 641, 2, (), 60), ("sphere", 800, 3, (), 60)])
+def test_runs_too_short_for_the_gang(fit, N, D, off, on):
+    """Runs that the step launches or the one-workgroup run finish sooner (the
+    state's way on and off the chip, or a meeting in most iterations)."""
+    announce(f"short runs {fit} N={N} D={D}")
+    with gpu_swarm(wl.SwarmSpec(fit, N, D, 1, seed=N + D)) as g:
+        for T in off:
+            g.reset()
+            g.run(T)
+        assert g.run_paths() == dict(resident=0, held=0, other=sum(off))
+        g.reset()
+        g.run(on)
+        assert g.run_paths() == dict(resident=on, held=0, other=sum(off))
