@@ -35,15 +35,17 @@ __host__ __device__ inline ResidentSplit resident_split(uint64_t N, int D)
     return ResidentSplit{L, cs, P, (uint32_t)((N + P - 1) / P)};
 }
 // Whether holding a swarm of `parts` parts in registers beats staging it in
-// LDS, in a launch of `total` parts in all on `grid` workgroups (200
-// iterations of Rastrigin; registers against LDS in ms):
+// LDS, in a launch of `total` parts in all on `grid` workgroups (registers
+// against LDS in ms, 200 iterations of Rastrigin where nothing else is said):
 //  - Parts that have a compute unit to themselves: a swarm of one or two parts
 //    is faster on the 1024 lanes of the LDS-staged kernel (one swarm, D = 30,
-//    N = 200: 1.17 against 1.00; N = 16: 0.66 / 0.48) unless D <= 4 (N = 200,
-//    D = 2: 0.78 of it), as is one that is several parts here and one there at
-//    D <= 2 (N = 1000, D = 1: 0.42 / 0.35).  Larger swarms gain from being
-//    split further (N = 4000, D = 10: 0.59 of LDS's time, D = 2: 0.41;
-//    N = 200, D = 48: 0.95).
+//    N = 200: 1.17 against 1.00; N = 16: 0.66 / 0.48), as is one that is several
+//    parts here, which meet, and one there (D <= 2, N = 1000: 0.42 / 0.35; 100
+//    iterations, D = 3: N = 128 1.15 of LDS's time, 300 1.46, 640 1.24; D = 8: 300
+//    1.43, 512 1.10; D = 16: 300 1.39), unless it is one part and D <= 2 (N = 200:
+//    0.95 of it).  Larger swarms gain from being split further (100 iterations,
+//    N = 1024: D = 3 0.93, 8 0.70; N = 640: D = 8 1.01, 16 0.91; N = 300, D = 20 0.98;
+//    N = 200, D = 40 0.89).
 //  - Parts that outnumber the workgroups at D <= 4: a register part holds 256
 //    particles, an LDS part thousands, and meets as often (300 swarms of
 //    N = 16000, D = 1: 18.0 / 9.4; D = 4: 20.0 / 18.3; D = 6: 0.88 of it).
@@ -51,7 +53,10 @@ __host__ __device__ inline ResidentSplit resident_split(uint64_t N, int D)
 //    N = 200, D = 30: 0.91.
 inline bool registers_pay(uint64_t N, int D, uint64_t parts, uint64_t total, int grid)
 {
-    if (total <= (uint64_t)(grid / RESIDENT_PER_CU)) return D <= 2 ? N <= 256 || N > 1024 : D <= 4 || N > 256 || parts > 2;
+    if (total <= (uint64_t)(grid / RESIDENT_PER_CU)) {
+        if (D <= 2) return N <= 256 || N > 1024;
+        return D <= RESIDENT_C ? N > (D <= 8 ? 640 : 512) : N > 256 || parts > 2;
+    }
     return !(D <= 4 && parts > 1 && total > (uint64_t)grid);
 }
 

@@ -104,3 +104,13 @@ def test_runs_too_short_for_the_gang(fit, N, D, off, on):
         g.reset()
         g.run(on)
         assert g.run_paths() == dict(resident=on, held=0, other=sum(off))
+
+
+@pytest.mark.parametrize("N,D,registers", [(256, 2, True), (257, 2, False), (1025, 2, True), (64, 3, False), (300, 3, False), (640, 8, False),
+                                           (641, 8, True), (512, 16, False), (513, 16, True), (257, 17, True), (300, 5, False)])
+def test_one_swarm_batches_in_registers(N, D, registers):
+    """A swarm that has the device to itself, on both sides of the lines
+    between the 1024-lane workgroup and parts that meet."""
+    announce(f"batch of one swarm N={N} D={D}")
+    with pso.Batch([wl.SwarmSpec("rastrigin", N, D, 10, seed=N)]) as b:
+        assert b.in_registers == registers
