@@ -118,6 +118,7 @@ struct pso_swarm {
     size_t gang_words_n = 0;
     // iterations that pso_run ran as a resident gang, held, and elsewhere
     uint64_t ran_resident = 0, ran_held = 0, ran_other = 0;
+    int64_t t = 0; // iterations enqueued since Step 1 (fewer ran where a stop rule held)
 };
 
 namespace {
@@ -161,6 +162,7 @@ int enqueue_init(pso_swarm *s)
 {
     HIP_TRY(pso::launch_reset(s->args, s->stream));
     HIP_TRY(pso::launch_init(s->fitness, s->args, s->stream));
+    s->t = 0;
     return PSO_OK;
 }
 
@@ -402,7 +404,7 @@ int gang_run(pso_swarm *s, int64_t *left, bool *fetched)
         if (getenv(name)) return PSO_OK;
     if (!pso::gang_accepts(s->fitness, s->args, s->shift_max, s->state_set)) return PSO_OK;
     pso::HoldShape hs;
-    const bool hold = !pso::gang_shape(s->fitness, s->args, *left, &sh); // too large to be held whole
+    const bool hold = !pso::gang_shape(s->fitness, s->args, s->t, *left, &sh); // too large to be held whole
     if (hold && !pso::hold_shape(s->fitness, s->args, *left, &hs)) return PSO_OK;
     const size_t n = hold ? pso::hold_words(s->D) : pso::gang_words(sh.G, s->D);
     if (n > s->gang_words_n) {
@@ -455,6 +457,7 @@ int pso_step(pso_swarm *s)
 {
     return pso::guarded([&]() -> int {
         if (!s) return fail(PSO_EINVAL, "swarm is NULL");
+        ++s->t;
         if (s->variant == PSO_PERSISTENT) return persistent_launch(s, 1);
         HIP_TRY(pso::launch_step(s->fitness, s->variant, s->args, s->stream));
         return PSO_OK;
@@ -542,6 +545,7 @@ int pso_run(pso_swarm *s, int64_t max_iter, float tol, float f_star, float *gbes
         if (gbest_pos_host) std::memcpy(gbest_pos_host, s->host_gpos, sizeof(float) * s->D);
         if (gbest_iter) *gbest_iter = c.giter;
         if (iters_done) *iters_done = c.t - c.t_run0;
+        s->t = c.t;
         s->ran_other += (uint64_t)(c.t - c.t_run0) - (s->ran_resident + s->ran_held - on_chip);
         return PSO_OK;
     });
@@ -615,6 +619,7 @@ int pso_set_state(pso_swarm *s, const float *x_host, const float *v_host, const 
         if ((gbest_key & 0xFFFFFFFFull) >= s->N) return fail(PSO_EINVAL, "gbest index out of range");
         HIP_TRY(hipStreamSynchronize(s->stream));
         s->state_set = true;
+        s->t = iters_completed;
         const size_t row = sizeof(float) * s->N, pitch = sizeof(float) * s->L.Np;
         HIP_TRY(hipMemcpy2D(s->args.x, pitch, x_host, row, row, s->D, hipMemcpyHostToDevice));
         HIP_TRY(hipMemcpy2D(s->args.v, pitch, v_host, row, row, s->D, hipMemcpyHostToDevice));

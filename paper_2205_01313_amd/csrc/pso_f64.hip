@@ -1217,6 +1217,7 @@ struct pso_swarm64 {
     pso::Fetch64 *host = nullptr, *host_dev = nullptr; // pinned, D doubles behind it; its device address (null: copied)
     // iterations that pso64_run ran as a resident gang, held, and elsewhere
     uint64_t ran_resident = 0, ran_held = 0, ran_other = 0;
+    int64_t t = 0; // iterations enqueued since Step 1 (fewer ran where a stop rule held)
 };
 
 namespace {
@@ -1281,6 +1282,7 @@ int reinit64(pso_swarm64 *s)
 {
     HIP64_TRY(pso::launch64_reset(s->a, s->stream));
     HIP64_TRY(pso::launch64_init(s->fitness, s->a, s->stream));
+    s->t = 0;
     return PSO_OK;
 }
 
@@ -1303,7 +1305,7 @@ int gang_run64(pso_swarm64 *s, const char *path, int64_t *left, bool *absent, ps
     pso::Gang64Shape sh;
     if (!pso::gang64_accepts(s->fitness, s->a)) return PSO_OK;
     pso::HoldShape hs;
-    const bool hold = !pso::gang64_shape(s->fitness, s->a, *left, &sh); // too large to be held whole
+    const bool hold = !pso::gang64_shape(s->fitness, s->a, s->t, *left, &sh); // too large to be held whole
     if (hold && (path || (getenv("PSO64_GANG_SHAPE") && !getenv("PSO_HOLD")) ||
                  !pso::hold_shape(s->fitness, s->a, *left, &hs)))
         return PSO_OK;
@@ -1438,6 +1440,7 @@ int pso64_step(pso_swarm64 *s)
     return pso::guarded([&]() -> int {
         if (!s) return pso_internal_fail(PSO_EINVAL, "swarm is NULL");
         HIP64_TRY(pso::launch64_step(s->fitness, s->a, s->stream));
+        ++s->t;
         return PSO_OK;
     });
 }
@@ -1493,6 +1496,7 @@ int pso64_run(pso_swarm64 *s, int64_t max_iter, double tol, double f_star, doubl
         if (c.err) return pso_internal_fail(PSO_EDEVICE, "a gang wait gave up (device error bits 0x%x)", c.err);
         if (gbest_iter) *gbest_iter = c.giter;
         if (iters_done) *iters_done = c.t - c.run_t0;
+        s->t = c.t;
         s->ran_other += (uint64_t)(c.t - c.run_t0) - (s->ran_resident + s->ran_held - on_chip);
         return PSO_OK;
     });

@@ -91,7 +91,7 @@ struct Gang64Shape {
 };
 constexpr int GANG64_MAX_D_ALL = 512; // no instantiation holds more dimensions
 bool gang64_accepts(int fitness, const Swarm64Args &a);
-bool gang64_shape(int fitness, const Swarm64Args &a, int64_t T, Gang64Shape *out);
+bool gang64_shape(int fitness, const Swarm64Args &a, int64_t t0, int64_t T, Gang64Shape *out);
 size_t gang64_words(uint64_t N, int D); // 64-bit words reserved in the swarm's memory
 // What a run returns, as k_fetch64 writes it to pinned host memory; the gbest
 // position (D doubles) follows.

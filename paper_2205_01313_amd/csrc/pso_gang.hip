@@ -775,7 +775,7 @@ static bool gang_layout(int fitness, const SwarmArgs &a, int cus, int lds_max, i
 //   larger chunks where smaller ones need more lanes than a part has: N =
 //     65536: D = 64 C = 16 10.1 / 15.1 (C = 64) / 23.3; D = 128 C = 64 19.9 /
 //     39.2; N = 262144: D = 16 8.3 / 25.2, D = 30 C = 32 16.2 / 37.9
-bool gang_shape(int fitness, const SwarmArgs &a, int64_t T, GangShape *out)
+bool gang_shape(int fitness, const SwarmArgs &a, int64_t t0, int64_t T, GangShape *out)
 {
     int cus = 0, lds_max = 0;
     if (!gang_device(&cus, &lds_max)) return false;
@@ -793,13 +793,16 @@ bool gang_shape(int fitness, const SwarmArgs &a, int64_t T, GangShape *out)
     // Sphere D = 2, T = 300: N = 641 445 / 331, 1024 475 / 375; N = 1500 T = 100
     // 223 / 185; Ackley N = 600, D = 2, T = 100 207 / 182, N = 800, D = 1 195 / 175);
     // at T = 600 the two are level, and Rastrigin and Cubic settle too early.
+    // Iterations count from Step 1: a run that goes on from one before it has
+    // settled (Sphere D = 2, N = 1000, 200 iterations more: 120 / 240).
     const bool late = settles_late(fitness);
-    if (late && D == 2 && N > 640 && N <= 1600 && T < (N <= 1300 ? 500 : 300)) return false;
-    if (fitness == F_ACKLEY && D <= 2 && N > 384 && N <= 1024 && T < 200) return false;
+    const int64_t end = t0 + T;
+    if (late && D == 2 && N > 640 && N <= 1600 && end < (N <= 1300 ? 500 : 300)) return false;
+    if (fitness == F_ACKLEY && D <= 2 && N > 384 && N <= 1024 && end < 200) return false;
     // A brief run stays in one part longer (settles_late; us of 200 iterations, one
     // part / more: Rosenbrock D = 3, N = 800 400 / 490; Rastrigin D = 2, N = 641
     // 203 / 196, of 100 137 / 146; Sphere D = 2, N = 641 of 600 621 / 697).
-    const bool brief = T < 200, longer = late && T < 800;
+    const bool brief = end < 200, longer = late && end < 800;
     const uint32_t most2 = brief ? 1024 : longer && D == 2 ? 768 : 640, most4 = brief || longer ? 960 : 768;
     if (one_part(N, D, most2, most4, 256, [&](int c, uint32_t P) { return layout(c, P, out); })) return true;
     // Several parts: the state's way in and out of the registers and the

@@ -65,8 +65,9 @@ struct GangShape {
 // ranges its shorter instruction sequences are exact for; shift_max: largest
 // magnitude of the shift vector; state_set: pso_set_state was called).
 bool gang_accepts(int fitness, const SwarmArgs &a, float shift_max, bool state_set);
-// The swarm's shape for a run of T iterations, or false if none holds it.
-bool gang_shape(int fitness, const SwarmArgs &a, int64_t T, GangShape *out);
+// The swarm's shape for a run of T iterations, t0 after Step 1, or false if none
+// holds it or other paths are faster.
+bool gang_shape(int fitness, const SwarmArgs &a, int64_t t0, int64_t T, GangShape *out);
 // 64-bit device words of the meeting.
 size_t gang_words(uint32_t parts, int D);
 // Sphere and Rosenbrock go down one valley and improve their gbest in most of

@@ -692,7 +692,7 @@ static bool gang64_layout(int fitness, const Swarm64Args &a, int cus, int lds_ma
 // 24.5; larger chunks: Cubic 16384, 120 C = 8 12.9 / 14.1 / 32.5; Rosenbrock
 // 32768, 120 C = 32 16.9 / - / 46.4, Rastrigin 65536, 30 C = 16 15.6 / 24.7 (C =
 // 8, which spills) / 40.8.
-bool gang64_shape(int fitness, const Swarm64Args &a, int64_t T, Gang64Shape *out)
+bool gang64_shape(int fitness, const Swarm64Args &a, int64_t t0, int64_t T, Gang64Shape *out)
 {
     int cus = 0, lds_max = 0;
     if (!gang_device(&cus, &lds_max)) return false;
@@ -711,7 +711,7 @@ bool gang64_shape(int fitness, const Swarm64Args &a, int64_t T, Gang64Shape *out
     // D = 2, N = 641 1535 / 1797 / 1694, N = 1024 1789 / 1774 / 1932; Rosenbrock D = 3,
     // N = 800 2490 / 2953 / 2648); Rastrigin and Ackley leave it at once, a brief run
     // of Cubic stays (of 100 iterations, Ackley N = 900, D = 1 339 / 269 / 329).
-    const bool late = settles_late(fitness), brief = T < 200;
+    const bool late = settles_late(fitness), brief = t0 + T < 200;
     const uint32_t most2 = heavy ? 640 : brief ? 1024 : late && D == 2 ? 768 : 640;
     const uint32_t most4 = late ? 1024 : brief ? 960 : 768;
     if (one_part(N, D, most2, most4, 0, [&](int c, uint32_t P) {

@@ -114,3 +114,19 @@ def test_one_swarm_batches_in_registers(N, D, registers):
     announce(f"batch of one swarm N={N} D={D}")
     with pso.Batch([wl.SwarmSpec("rastrigin", N, D, 10, seed=N)]) as b:
         assert b.in_registers == registers
+
+
+def test_run_that_goes_on_is_not_short():
+    """What the short runs' rule is for is over when a swarm has settled: a
+    short run 500 iterations after Step 1 stays on the chip, after a reset not."""
+    announce("short run of a settled swarm")
+    with gpu_swarm(wl.SwarmSpec("sphere", 1000, 2, 1, seed=3)) as g:
+        g.run(600)
+        g.run(100)
+        assert g.run_paths() == dict(resident=700, held=0, other=0)
+        g.reset()
+        g.run(100)
+        assert g.run_paths() == dict(resident=700, held=0, other=100)
+        g.step(400)
+        g.run(100)
+        assert g.run_paths() == dict(resident=800, held=0, other=100)
