@@ -134,19 +134,21 @@ int pso_step(pso_swarm *s);
  * initialisation) and the number of iterations this call ran.  Any output
  * pointer may be NULL.  A synchronous swarm that fits the device's vector
  * registers and LDS (N*D up to about 8 million, D <= 512, N <= 262144) runs
- * as launches of up to 256 co-resident workgroups (about 50 ms each) that
- * keep it there and meet once per iteration, or once per block of iterations
- * while the gbest does not change; a larger one (N up to 4 million, D <= 512,
- * max_iter >= 8) whose registers and LDS hold a tenth of it or more as such
- * launches that keep that part there and stream the rest (PSO_HOLD=0 in the
- * environment: not).  If the workgroups are not resident
- * together within 2 ms (another kernel holds the device) nothing has run and
- * the call goes on as below; a workgroup that is lost later (20 s) sets a
- * device error, returned as PSO_EDEVICE.  PSO_GANG=0 in the environment turns
- * this off.  Else a synchronous swarm with N*D <= 65536 whose state fits one
- * workgroup's LDS runs the whole call as one launch of one workgroup, and
- * others take one launch per iteration (PSO_PERSISTENT: one persistent
- * launch).
+ * as launches of up to 256 co-resident workgroups (about 10 ms each where they
+ * take more than half of the compute units, else about 20 ms) that keep it
+ * there and meet once per iteration, or once per block of iterations while the
+ * gbest does not change; a larger one (N up to 4 million, D <= 512, max_iter >=
+ * 8), of which registers and LDS hold a tenth or more, as such launches that
+ * keep that part there and stream the rest (PSO_HOLD=0 in the environment:
+ * not).  The shortest runs of some sizes take the paths below, which finish them
+ * sooner.  If the workgroups are not resident together within 0.5 ms (another
+ * kernel holds the device) nothing has run, and the call goes on as below for
+ * about 20 ms of launches before it tries again; a workgroup that is lost later
+ * (20 s) sets a device error, returned as PSO_EDEVICE.  PSO_GANG=0 in the
+ * environment turns this off (in pso_run).  Else a synchronous swarm with N*D <=
+ * 65536 whose state fits one workgroup's LDS runs the whole call as one launch
+ * of one workgroup, and others take one launch per iteration (PSO_PERSISTENT:
+ * one persistent launch).
  * Every path computes the same bits. */
 int pso_run(pso_swarm *s, int64_t max_iter, float tol, float f_star, float *gbest_value,
             float *gbest_pos_host, int64_t *gbest_iter, int64_t *iters_done);
@@ -233,8 +235,8 @@ int pso64_step(pso_swarm64 *s);
  * that fits the device's vector registers (N*D up to about 4 million, D <=
  * 256, N <= 262144) runs as launches of up to 256 co-resident workgroups as in
  * pso_run, a larger one (N up to 4 million, D <= 512, max_iter >= 3) as such
- * launches that keep part of it there (not resident together within 2 ms: the
- * paths below).  Else a swarm
+ * launches that keep part of it there (not resident together within 0.5 ms: the
+ * paths below, as there; PSO64_PATH=grid in the environment: the grid step).  Else a swarm
  * with D >= 32 and N <= 32768 launches one grid step per iteration (lanes
  * share each particle's dimensions); else a swarm whose x, v, p and pbest
  * fitness fit one workgroup's LDS ((3D+1)*N doubles, up to about 160 KiB)

@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <chrono>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -389,14 +390,11 @@ int enqueue_steps(pso_swarm *s, int64_t n)
 
 // Runs the swarm's next iterations as a resident gang, or with part of the
 // state held on the chip (pso_hold.hip), where that suits it, and takes what it
-// ran off *left (the rest is for the other paths).  The stop rule is armed; *fetched: the host's copies of the control block and the
-// gbest position are those of the run's end.  A launch is kept to about
-// GANG_LAUNCH_US (an iteration takes at most about 1 us and 2.5 us per million
-// particle-dimensions) so that other work on the device waits no longer for
-// its compute units.
-constexpr double GANG_LAUNCH_US = 50000.0;
-
-int gang_run(pso_swarm *s, int64_t *left, bool *fetched)
+// ran off *left (the rest is for the other paths).  The stop rule is armed, and
+// with `armed` the rendezvous too; *absent: its parts were not resident together;
+// *fetched: the host's copies of the control block and the gbest position are
+// those of the run's end.
+int gang_run(pso_swarm *s, int64_t *left, bool armed, bool *absent, bool *fetched)
 {
     pso::GangShape sh;
     // a path forced from the environment is meant
@@ -419,16 +417,21 @@ int gang_run(pso_swarm *s, int64_t *left, bool *fetched)
         }
         s->gang_words_n = n;
     }
-    const int64_t most = std::max<int64_t>(64, std::min<int64_t>(pso::GANG_MAX_T, int64_t(GANG_LAUNCH_US / (1.0 + 2.5e-6 * double(s->N) * s->D))));
-    int64_t counted = 0;
-    for (bool first = true; *left > 0; first = false) {
-        const int64_t T = std::min(*left, most);
-        if (!first) HIP_TRY(pso::launch_gang_arm(s->args, s->stream));
+    pso::LaunchLength length{pso::launch_us(hold ? hs.G : sh.G), pso::gang_iteration_us((double)s->N, s->D, hold, false)};
+    int64_t counted = armed ? 0 : s->host_ctrl->t - s->host_ctrl->t_run0;
+    for (; *left > 0; armed = false) {
+        const int64_t T = length.next(*left);
+        const auto start = std::chrono::steady_clock::now();
+        if (!armed) HIP_TRY(pso::launch_gang_arm(s->args, s->stream));
         HIP_TRY(hold ? pso::launch_hold(s->args, hs, (uint32_t)T, s->gang_words, s->stream)
                      : pso::launch_gang(s->args, sh, (uint32_t)T, s->gang_words, s->stream));
         int rc = fetch_ctrl(s, true);
         if (rc) return rc;
-        if (s->host_ctrl->gang_state == pso::GANG_ABSENT) break;
+        if (s->host_ctrl->gang_state == pso::GANG_ABSENT) {
+            *absent = true;
+            break;
+        }
+        length.took(T, std::chrono::duration<double, std::micro>(std::chrono::steady_clock::now() - start).count());
         const int64_t ran = s->host_ctrl->t - s->host_ctrl->t_run0;
         (hold ? s->ran_held : s->ran_resident) += (uint64_t)(ran - counted);
         counted = ran;
@@ -449,6 +452,76 @@ int persistent_launch(pso_swarm *s, int64_t T)
         T -= n;
     }
     return PSO_OK;
+}
+
+// A synchronous swarm small enough for the one-workgroup run.
+bool one_workgroup(const pso_swarm *s)
+{
+    return s->variant == PSO_SYNC && int64_t(s->N) * s->D <= BLOCK_RUN_MAX_ND && pso::block_run_suits(s->fitness, s->args);
+}
+
+// Iterations of the other paths before the gang is tried again, whose wait for
+// its parts was in vain: about 20 ms of step launches (a step takes 8 us and
+// about 4.5 us per million particle-dimensions), 40 of those waits.
+int64_t between_gangs(const pso_swarm *s)
+{
+    return one_workgroup(s) ? INT64_MAX : std::max<int64_t>(1, int64_t(20000.0 / (8.0 + 4.5e-6 * double(s->N) * s->D)));
+}
+
+// The paths of pso_run below the gang: T iterations, of which the device skips
+// those after its stop rule holds (synchronous only with tol > 0).
+int step_run(pso_swarm *s, int64_t T, float tol)
+{
+    if (s->variant == PSO_PERSISTENT) return persistent_launch(s, T);
+    if (one_workgroup(s)) {
+        if (T > 0) HIP_TRY(pso::launch_block_run(s->fitness, s->args, T, s->stream));
+        return PSO_OK;
+    }
+    if (!(tol > 0.0f)) return enqueue_steps(s, T);
+    // Chunks of iterations with one chunk always queued ahead; the
+    // device skips iterations once the stop rule holds, and the host
+    // stops enqueueing when it sees the flag.
+    const double work = double(s->N) * double(s->D);
+    const int64_t chunk =
+        std::max<int64_t>(8, std::min<int64_t>(256, int64_t((1 << 26) / work))) / RUN_GRAPH_STEPS *
+        RUN_GRAPH_STEPS;
+    hipEvent_t ev[2];
+    HIP_TRY(hipEventCreateWithFlags(&ev[0], hipEventDisableTiming));
+    if (hipEventCreateWithFlags(&ev[1], hipEventDisableTiming) != hipSuccess) {
+        (void)hipEventDestroy(ev[0]);
+        return fail(PSO_EDEVICE, "hipEventCreate failed");
+    }
+    unsigned int *flags = nullptr;
+    if (hipHostMalloc(reinterpret_cast<void **>(&flags), 2 * sizeof(unsigned int), hipHostMallocDefault) !=
+        hipSuccess) {
+        (void)hipEventDestroy(ev[0]);
+        (void)hipEventDestroy(ev[1]);
+        return fail(PSO_ENOMEM, "pinned host allocation failed");
+    }
+    int rc = PSO_OK;
+    int64_t done = 0;
+    int k = 0, inflight = 0;
+    while (done < T && rc == PSO_OK) {
+        const int64_t n = std::min(chunk, T - done);
+        rc = enqueue_steps(s, n);
+        done += n;
+        if (hipMemcpyAsync(&flags[k], &s->args.ctrl->stop, sizeof(unsigned int), hipMemcpyDeviceToHost,
+                           s->stream) != hipSuccess ||
+            hipEventRecord(ev[k], s->stream) != hipSuccess)
+            rc = fail(PSO_EDEVICE, "stop flag copy failed");
+        ++inflight;
+        k ^= 1;
+        if (inflight == 2) { // wait for the older chunk
+            if (hipEventSynchronize(ev[k]) != hipSuccess) rc = fail(PSO_EDEVICE, "event wait failed");
+            --inflight;
+            if (flags[k]) break;
+        }
+    }
+    (void)hipStreamSynchronize(s->stream);
+    (void)hipHostFree(flags);
+    (void)hipEventDestroy(ev[0]);
+    (void)hipEventDestroy(ev[1]);
+    return rc;
 }
 
 } // namespace
@@ -474,69 +547,28 @@ int pso_run(pso_swarm *s, int64_t max_iter, float tol, float f_star, float *gbes
         HIP_TRY(pso::launch_arm(s->args, tol, f_star, s->stream));
         const uint64_t on_chip = s->ran_resident + s->ran_held; // before this run
         bool fetched = false;
-        if (s->variant == PSO_SYNC && max_iter > 0) {
-            // the gang runs what it can; max_iter keeps what is left for the
-            // other paths (all of it where its parts were not resident)
-            int rc = gang_run(s, &max_iter, &fetched);
-            if (rc) return rc;
-        }
-        const bool block_path = s->variant == PSO_SYNC && int64_t(s->N) * s->D <= BLOCK_RUN_MAX_ND &&
-                                pso::block_run_suits(s->fitness, s->args);
-        if (fetched) {
-            // the gang ran it all
-        } else if (s->variant == PSO_PERSISTENT) {
-            int rc = persistent_launch(s, max_iter);
-            if (rc) return rc;
-        } else if (block_path) {
-            if (max_iter > 0) HIP_TRY(pso::launch_block_run(s->fitness, s->args, max_iter, s->stream));
-        } else if (tol > 0.0f) {
-            // Chunks of iterations with one chunk always queued ahead; the
-            // device skips iterations once the stop rule holds, and the host
-            // stops enqueueing when it sees the flag.
-            const double work = double(s->N) * double(s->D);
-            const int64_t chunk =
-                std::max<int64_t>(8, std::min<int64_t>(256, int64_t((1 << 26) / work))) / RUN_GRAPH_STEPS *
-                RUN_GRAPH_STEPS;
-            hipEvent_t ev[2];
-            HIP_TRY(hipEventCreateWithFlags(&ev[0], hipEventDisableTiming));
-            if (hipEventCreateWithFlags(&ev[1], hipEventDisableTiming) != hipSuccess) {
-                (void)hipEventDestroy(ev[0]);
-                return fail(PSO_EDEVICE, "hipEventCreate failed");
+        int64_t left = max_iter;
+        for (bool armed = true;; armed = false) {
+            // the gang runs what it can
+            bool absent = false;
+            if (s->variant == PSO_SYNC && left > 0) {
+                int rc = gang_run(s, &left, armed, &absent, &fetched);
+                if (rc) return rc;
             }
-            unsigned int *flags = nullptr;
-            if (hipHostMalloc(reinterpret_cast<void **>(&flags), 2 * sizeof(unsigned int), hipHostMallocDefault) !=
-                hipSuccess) {
-                (void)hipEventDestroy(ev[0]);
-                (void)hipEventDestroy(ev[1]);
-                return fail(PSO_ENOMEM, "pinned host allocation failed");
-            }
-            int rc = PSO_OK;
-            int64_t done = 0;
-            int k = 0, inflight = 0;
-            while (done < max_iter && rc == PSO_OK) {
-                const int64_t n = std::min(chunk, max_iter - done);
-                rc = enqueue_steps(s, n);
-                done += n;
-                if (hipMemcpyAsync(&flags[k], &s->args.ctrl->stop, sizeof(unsigned int), hipMemcpyDeviceToHost,
-                                   s->stream) != hipSuccess ||
-                    hipEventRecord(ev[k], s->stream) != hipSuccess)
-                    rc = fail(PSO_EDEVICE, "stop flag copy failed");
-                ++inflight;
-                k ^= 1;
-                if (inflight == 2) { // wait for the older chunk
-                    if (hipEventSynchronize(ev[k]) != hipSuccess) rc = fail(PSO_EDEVICE, "event wait failed");
-                    --inflight;
-                    if (flags[k]) break;
-                }
-            }
-            (void)hipStreamSynchronize(s->stream);
-            (void)hipHostFree(flags);
-            (void)hipEventDestroy(ev[0]);
-            (void)hipEventDestroy(ev[1]);
+            if (fetched) break;
+            // and the other paths the rest, or a while of it where its parts were
+            // not resident together: whatever held the device may have ended then
+            const int64_t n = absent ? std::min(left, between_gangs(s)) : left;
+            int rc = step_run(s, n, tol);
             if (rc) return rc;
-        } else {
-            int rc = enqueue_steps(s, max_iter);
+            left -= n;
+            if (left == 0) break;
+            rc = fetch_ctrl(s, true);
             if (rc) return rc;
+            if (s->host_ctrl->stop) {
+                fetched = true;
+                break;
+            }
         }
         int rc = fetched ? PSO_OK : fetch_ctrl(s, true);
         if (rc) return rc;

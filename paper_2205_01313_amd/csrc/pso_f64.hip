@@ -17,6 +17,7 @@
 // the improved particles into its own slot, and the last workgroup to arrive
 // reduces the slots (lowest index among equal fitness).
 #include <algorithm>
+#include <chrono>
 #include <cmath>
 #include <cstdlib>
 #include <cstring>
@@ -1288,13 +1289,11 @@ int reinit64(pso_swarm64 *s)
 
 // Runs the swarm's next iterations as a resident gang, or with part of the
 // state held on the chip (pso_hold.hip), where that suits it, and takes what it
-// ran off *left; *absent: its parts were not resident together, so no other
-// gang is tried either; *fetched: it ran them all, and *ctrl, *value and pos
-// hold the results.  A launch is kept to about 50 ms
-// (an iteration takes at most about 1.5 us and 10 us per million
-// particle-dimensions) so that other work on the device waits no longer.
-int gang_run64(pso_swarm64 *s, const char *path, int64_t *left, bool *absent, pso::Ctrl64 *ctrl, double *value,
-               double *pos, bool *fetched)
+// ran off *left; armed: launch64_arm has just run, else *ctrl is of the
+// iterations so far; *absent: its parts were not resident together; *fetched: it
+// ran them all, and *ctrl, *value and pos hold the results.
+int gang_run64(pso_swarm64 *s, const char *path, int64_t *left, bool armed, bool *absent, pso::Ctrl64 *ctrl,
+               double *value, double *pos, bool *fetched)
 {
     const char *staged = getenv("PSO64_GANG_STAGED");
     if (path && (strcmp(path, "gang") || (staged && !strcmp(staged, "0")))) return PSO_OK;
@@ -1309,12 +1308,13 @@ int gang_run64(pso_swarm64 *s, const char *path, int64_t *left, bool *absent, ps
     if (hold && (path || (getenv("PSO64_GANG_SHAPE") && !getenv("PSO_HOLD")) ||
                  !pso::hold_shape(s->fitness, s->a, *left, &hs)))
         return PSO_OK;
-    int64_t counted = 0;
-    const int64_t most =
-        std::max<int64_t>(64, std::min<int64_t>(pso::GANG_MAX_T, int64_t(50000.0 / (1.5 + 1e-5 * double(s->N) * s->D))));
-    for (bool first = true; *left > 0; first = false) {
-        const int64_t T = std::min(*left, most);
-        if (!first) HIP64_TRY(pso::launch64_gang_arm(s->a, s->stream));
+    const int64_t before = armed ? 0 : ctrl->t - ctrl->run_t0;
+    int64_t counted = before;
+    pso::LaunchLength length{pso::launch_us(hold ? hs.G : sh.G), pso::gang_iteration_us((double)s->N, s->D, hold, true)};
+    for (; *left > 0; armed = false) {
+        const int64_t T = length.next(*left);
+        const auto start = std::chrono::steady_clock::now();
+        if (!armed) HIP64_TRY(pso::launch64_gang_arm(s->a, s->stream));
         HIP64_TRY(hold ? pso::launch_hold(s->a, hs, (uint32_t)T, s->stream)
                        : pso::launch_gang64(s->fitness, s->a, sh, (uint32_t)T, s->stream));
         pso::Ctrl64 &c = *ctrl;
@@ -1324,6 +1324,7 @@ int gang_run64(pso_swarm64 *s, const char *path, int64_t *left, bool *absent, ps
             *absent = true;
             break;
         }
+        length.took(T, std::chrono::duration<double, std::micro>(std::chrono::steady_clock::now() - start).count());
         const int64_t ran = c.t - c.run_t0;
         (hold ? s->ran_held : s->ran_resident) += (uint64_t)(ran - counted);
         counted = ran;
@@ -1331,8 +1332,16 @@ int gang_run64(pso_swarm64 *s, const char *path, int64_t *left, bool *absent, ps
         *fetched = *left == 0;
     }
     // the narrow grid step takes no pending pbest position
-    if (hold && counted > 0) HIP64_TRY(pso::launch64_flush(s->a, s->stream));
+    if (hold && counted > before) HIP64_TRY(pso::launch64_flush(s->a, s->stream));
     return PSO_OK;
+}
+
+// Iterations of the grid step before the resident gang is tried again, whose
+// wait for its parts was in vain: about 20 ms of them (8 us and about 15 us per
+// million particle-dimensions each), 40 of those waits.
+int64_t between_gangs64(const pso_swarm64 *s)
+{
+    return std::max<int64_t>(1, int64_t(20000.0 / (8.0 + 15e-6 * double(s->N) * s->D)));
 }
 
 // Pitched (Np) device rows -> dense (N) host rows.
@@ -1457,38 +1466,39 @@ int pso64_run(pso_swarm64 *s, int64_t max_iter, double tol, double f_star, doubl
         const uint64_t on_chip = s->ran_resident + s->ran_held; // before this run
         const uint64_t nd = s->N * (uint64_t)s->D;
         const char *path = getenv("PSO64_PATH"); // tests of every path: block, gang, grid
-        // the resident gang runs what it can; max_iter keeps what is left for
-        // the other paths (all of it where its parts were not resident)
-        bool absent = false;
-        if (max_iter > 0) {
-            int rc = gang_run64(s, path, &max_iter, &absent, &c, gbest_value, gbest_pos, &fetched);
+        for (bool armed = true; max_iter > 0; armed = false) {
+            // the resident gang runs what it can
+            bool absent = false;
+            int rc = gang_run64(s, path, &max_iter, armed, &absent, &c, gbest_value, gbest_pos, &fetched);
             if (rc) return rc;
-        }
-        bool done_gang = max_iter == 0;
-        const bool block = !done_gang && (path ? !strcmp(path, "block")
-                                               : !pso::step64_split(s->fitness, s->a) &&
-                                                     (pso::block64_staged_fits(s->a) || nd <= BLOCK64_MAX_ND));
-        const bool gang = !done_gang && !block && !absent &&
-                          (path ? !strcmp(path, "gang") : s->D <= GANG64_MAX_D);
-        // those paths write each pbest position at once: complete the
-        // pending ones a wide grid step left
-        if (block || gang) HIP64_TRY(pso::launch64_flush(s->a, s->stream));
-        if (block) {
-            HIP64_TRY(pso::launch64_block_run(s->fitness, s->a, max_iter, s->stream));
-            done_gang = true;
-        } else if (gang) {
-            HIP64_TRY(hipMemsetAsync(&s->a.ctrl->gang_arrive, 0, sizeof(unsigned long long), s->stream));
-            HIP64_TRY(pso::launch64_gang(s->fitness, s->a, max_iter, s->stream, &done_gang));
-        }
-        if (!done_gang) {
+            if (max_iter == 0) break;
+            // and the other paths the rest, or a while of it where its parts were
+            // not resident together: whatever held the device may have ended then
+            const bool block = path ? !strcmp(path, "block")
+                                    : !pso::step64_split(s->fitness, s->a) &&
+                                          (pso::block64_staged_fits(s->a) || nd <= BLOCK64_MAX_ND);
+            const bool gang = !block && !absent && (path ? !strcmp(path, "gang") : s->D <= GANG64_MAX_D);
+            // those paths write each pbest position at once: complete the
+            // pending ones a wide grid step left
+            if (block || gang) HIP64_TRY(pso::launch64_flush(s->a, s->stream));
+            bool done_gang = false;
+            if (block) {
+                HIP64_TRY(pso::launch64_block_run(s->fitness, s->a, max_iter, s->stream));
+                done_gang = true;
+            } else if (gang) {
+                HIP64_TRY(hipMemsetAsync(&s->a.ctrl->gang_arrive, 0, sizeof(unsigned long long), s->stream));
+                HIP64_TRY(pso::launch64_gang(s->fitness, s->a, max_iter, s->stream, &done_gang));
+            }
+            if (done_gang) break;
             // chunks of launches; every launch returns at once after the stop rule holds
-            for (int64_t done = 0; done < max_iter;) {
-                const int64_t n = std::min<int64_t>(256, max_iter - done);
+            int64_t most = absent ? std::min(max_iter, between_gangs64(s)) : max_iter;
+            for (max_iter -= most; most > 0;) {
+                const int64_t n = std::min<int64_t>(256, most);
                 for (int64_t k = 0; k < n; ++k) HIP64_TRY(pso::launch64_step(s->fitness, s->a, s->stream));
-                done += n;
+                most -= n;
                 HIP64_TRY(hipStreamSynchronize(s->stream));
                 HIP64_TRY(hipMemcpy(&c, s->a.ctrl, sizeof c, hipMemcpyDeviceToHost));
-                if (c.stop) break;
+                if (c.stop) most = max_iter = 0;
             }
         }
         if (!fetched)

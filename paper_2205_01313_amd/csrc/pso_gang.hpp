@@ -5,6 +5,7 @@
 #include <algorithm>
 
 #include "pso_kernels.hpp"
+#include "pso_launch_length.hpp"
 
 namespace pso {
 
@@ -13,8 +14,10 @@ constexpr unsigned int GANG_GO = 1u;     // all parts resident: the launch ran
 constexpr unsigned int GANG_ABSENT = 2u; // not all resident in time: nothing was touched
 
 constexpr unsigned long long GANG_TICKS = 2000000000ull;   // 20 s of the 100 MHz wall clock: a part is lost
-constexpr unsigned long long RENDEZVOUS_TICKS = 200000ull; // 2 ms: the parts are not resident together
-constexpr uint32_t GANG_PARTS_MAX = 256;                   // one byte of the meeting's minimum
+// 0.5 ms: the parts are not resident together.  All of them arrive within 0.05 ms
+// on an idle device, also after seconds of rest (but for a kernel's first launch);
+// what waits in vain holds compute units that another kernel could use.
+constexpr unsigned long long RENDEZVOUS_TICKS = 50000ull;
 constexpr int SPEC_MAX_K = 64;                             // iterations of a block at most (fits the word's 8 bits)
 constexpr int KEY_STRIDE = 8;                              // key words one per 64-byte line
 
@@ -50,7 +53,6 @@ struct GangArgs {
     float c1s, c2s;            // c1 2^-24, c2 2^-24 (exact)
     unsigned long long *words; // the parts' meeting words
 };
-constexpr uint32_t GANG_MAX_T = 1u << 23; // meetings are numbered in 24 bits
 
 // How a swarm is laid out over the parts: chunks of C dimensions, P particles
 // and P * L lanes per part (rounded up to whole wavefronts), G parts.
