@@ -361,7 +361,8 @@ int pso_batch_run_static(const pso_desc *descs, int64_t count, pso_result *resul
  * many parts as its state needs, at most 512 and at most the grid; swarms
  * that would need more stream, in a second kernel of the same launch.  A new
  * batch takes the shape pso_batch_autotune chose earlier in this process for
- * the same swarm sizes and iteration limits on the same device, else 1024
+ * the same swarm sizes and iteration limits on the same device (and parts that
+ * may be held in registers, or not, alike; below), else 1024
  * lanes with 158 KiB staged (less for D above 64: the LDS also holds
  * 2 x D floats) if every swarm fits that, else 256 lanes, the
  * full capacity, 2^17 updates per part, streamed.  Under a shape of 1024

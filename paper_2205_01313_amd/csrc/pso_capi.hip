@@ -997,6 +997,7 @@ int pso_batch_create(const pso_desc *descs, int64_t count, void *hip_stream, pso
         uint64_t max_entries = 0, sig = 1469598103934665603ull;
         auto mix = [&](uint64_t v) { sig = (sig ^ v) * 1099511628211ull; };
         mix((uint64_t)count);
+        mix(registers ? 1 : 0); // whole-unit shapes name another kernel then
         for (int64_t i = 0; i < count; ++i) {
             const pso_desc &d = descs[i];
             lay[i] = pso::layout_of((uint64_t)d.N, d.D, false);

@@ -308,3 +308,23 @@ def test_staged_launch_streams_swarms_too_large_to_stage():
         sp = specs[k]
         o = oracle_swarm(sp, 16).run_f32(sp.T, tol=getattr(sp, "tol", 0.0), f_star=getattr(sp, "f_star", 0.0))
         assert ref[k]["gbest_fit"] == o["gbest_fit"] and np.array_equal(ref[k]["gbest_pos"], o["gpos"]), sp
+
+
+def test_tuned_shapes_are_shared_by_batches_of_one_kernel():
+    """A shape tuned for a batch that cannot hold its parts in registers (an
+    upper bound of -0) says nothing about one of the same sizes that can."""
+    def specs(box):
+        return [wl.SwarmSpec("sphere", 300, 5, 50, seed=k, box=box) for k in range(1000)]
+
+    announce("tuned shapes by kernel")
+    with pso.Batch(specs((-1.0, 0.0))) as b:
+        assert b.in_registers
+        before = b.shape
+    with pso.Batch(specs((-1.0, -0.0))) as b:
+        assert not b.in_registers
+        tuned = b.autotune(8)
+    print(f"tuned {tuned}", flush=True)
+    with pso.Batch(specs((-1.0, -0.0))) as b:
+        assert b.shape == tuned
+    with pso.Batch(specs((-1.0, 0.0))) as b:
+        assert b.shape == before and b.in_registers
