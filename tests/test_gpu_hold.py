@@ -117,3 +117,27 @@ def test_held_runs_that_exclude_each_other():
         for r in out[k]:
             assert r["gbest_fit"] == alone[k]["gbest_fit"] and r["gbest_iter"] == alone[k]["gbest_iter"]
             assert np.array_equal(r["gbest_pos"], alone[k]["gbest_pos"])
+
+
+@pytest.mark.parametrize("wide,fit,N,D", [
+    (False, "sphere", 2000003, 4), (False, "cubic", 4000001, 3), (False, "ackley", 70001, 511), (False, "rosenbrock", 20011, 101),
+    (True, "rastrigin", 300001, 40), (True, "rosenbrock", 40001, 301), (True, "ackley", 20001, 101), (True, "cubic", 2000001, 2),
+    (True, "sphere", 9001, 512)])
+def test_held_runs_at_the_edges_of_what_they_accept(monkeypatch, wide, fit, N, D):
+    """Four and more groups of particles a lane, up to 512 dimensions, and
+    streamed rows that fit the memory-side cache or not, against the grid step."""
+    spec = wl.SwarmSpec(fit, N, D, 7, seed=N + D, shift_amplitude=1.0)
+    announce(f"held run {'binary64' if wide else 'binary32'} {fit} N={N} D={D}")
+    monkeypatch.setenv("PSO64_GANG_SHAPE" if wide else "PSO_GANG_SHAPE", "0,0")  # no gang of this shape
+    out = []
+    for hold in ("1", "0"):
+        monkeypatch.setenv("PSO_HOLD", hold)
+        make = pso.Swarm64 if wide else pso.Swarm
+        with make(fit, N, D, spec.box, spec.w, spec.c1, spec.c2, spec.vmax, 7, shift=spec.shift) as g:
+            r = [g.run(n) for n in (2, 5)][-1]
+            assert g.run_paths()["held"] == (7 if hold == "1" else 0)
+            out.append((r, g.state()))
+    (r, st), (r0, st0) = out
+    assert r["gbest_fit"] == r0["gbest_fit"] and r["gbest_iter"] == r0["gbest_iter"]
+    for key in st0:
+        assert np.array_equal(np.asarray(st[key]), np.asarray(st0[key])), key

@@ -303,3 +303,23 @@ def test_run_graph_replays_equal_oracle_and_direct_launches(monkeypatch, fit, N,
     with gpu_swarm(spec) as g:
         r = g.run(200, tol=tol, f_star=f_star)
     assert r["iters"] == os_["iters"] and r["gbest_fit"] == os_["gbest_fit"]
+
+
+@pytest.mark.parametrize("mk", [wl.deep_rosenbrock, wl.deep_ackley, wl.large_rastrigin])
+def test_full_runs_by_step_launches(monkeypatch, mk):
+    """The full-length runs above stay on the chip; here by step launches (the
+    split step at D = 128), against them: every iteration's gbest and the state."""
+    spec = mk(seed=0)
+    announce(f"step launches {spec.fitness} D={spec.D} N={spec.N} T={spec.T}")
+    out = []
+    for env in (None, "0"):
+        if env:
+            monkeypatch.setenv("PSO_GANG", env)
+        with gpu_swarm(spec) as g:
+            r = g.run(spec.T)
+            assert g.run_paths()["other"] == (spec.T if env else 0)
+            out.append((r, g.history(0, spec.T + 1), g.state()))
+    (r, hist, st), (r0, hist0, st0) = out
+    assert r["gbest_iter"] == r0["gbest_iter"] and np.array_equal(hist, hist0)
+    for key in st0:
+        assert np.array_equal(np.asarray(st[key]), np.asarray(st0[key])), key
