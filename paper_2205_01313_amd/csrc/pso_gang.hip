@@ -757,7 +757,9 @@ static bool gang_layout(int fitness, const SwarmArgs &a, int cus, int lds_max, i
 //   one part (no meeting; one_part) while its lanes hold the swarm: N = 40, D =
 //     20 1.8 / 2.1 / 2.1; 100, 12 1.85 / 2.6 / 2.24; 257, 5 1.92 / 2.2 / 2.2;
 //     624, 2 1.66 / 1.94 / 1.66 (60 iterations; 0.89 / 0.81 / 1.26 of 300);
-//     below N = 32 with D > 24 the one-workgroup run is 6 % faster
+//     of very few deep particles the one-workgroup run is faster, which has
+//     more lanes for each (100 iterations: Cubic N = 4, D = 130 455 / 336 us, Rastrigin
+//     N = 8, D = 250 643 / 505, N = 4, D = 24 185 / 165; level at N = 32, D = 40)
 //   D <= 2: 256 particles of a part, one lane each (C = 1 for D = 1): N =
 //     16384, D = 2 1.05 / 1.08 / 6.27
 //   D <= 4: pairs of lanes with few particles each, 32 of a part, below N =
@@ -787,7 +789,7 @@ bool gang_shape(int fitness, const SwarmArgs &a, int64_t t0, int64_t T, GangShap
     }
     const int D = a.D;
     const uint32_t N = a.N;
-    if (N < 32 && D > 24 && D <= 110) return false;
+    if ((N < 32 && D > 24) || (N <= 16 && D > 16)) return false;
     // Where the gbest changes in most iterations, no block of them pays for what
     // surrounds it, and the one-workgroup run is faster (us of a run, here / there:
     // Sphere D = 2, T = 300: N = 641 445 / 331, 1024 475 / 375; N = 1500 T = 100
