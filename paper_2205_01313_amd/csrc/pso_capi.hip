@@ -65,8 +65,8 @@ constexpr uint64_t MAX_BATCH_BYTES = uint64_t(1) << 52;
 // 5.2; Rastrigin D = 8, N = 2048: 13.7 / 10.7; D = 128, N = 512: 99.8 /
 // 14.0; Ackley D = 32, N = 1024: 26.2 / 9.8), so it runs only under
 // PSO_BLOCK_STAGED=0 (tests compare the two one-workgroup kernels).  The
-// resident gang takes every swarm it accepts before either, and held runs
-// most larger ones (gang_run).
+// resident gang and held runs come first (gang_run), but for the runs that they
+// would not finish sooner (gang_shape, hold_shape).
 #ifndef PSO_BLOCK_RUN_MAX_ND
 #define PSO_BLOCK_RUN_MAX_ND 65536
 #endif

@@ -1116,11 +1116,10 @@ static void block64_f(const Swarm64Args &a, long long T, hipStream_t s)
 }
 
 // Particles per lane of the gang kernel: fewer, fuller workgroups make the
-// per-iteration meeting cheaper (measured with the slices in LDS, Cubic 1D,
-// us per iteration at 1/2/4/8/16 particles per lane: N = 4096: 4.2/3.9/4.3/
-// 5.8/8.4; 8192: 5.2/4.6/4.6/5.8/8.6; 16384: 7.0/5.6/5.2/6.0/8.6; 65536:
-// 17.5/10.2/7.8/7.8/9.5; 131072: 37.9/18.1/12.2/9.7/10.7; in device memory
-// the same choices are within 2 % of the best).  PSO64_GANG_PPL overrides it.
+// per-iteration meeting cheaper (Cubic 1D, us per iteration at 1/2/4/8/16
+// particles per lane: N = 4096: 5.3/5.1/6.2/8.7/13.3; 8192: 6.2/5.8/6.4/8.8/13.9;
+// 16384: 8.2/6.8/7.0/9.0/13.9; 65536: 18.4/11.5/9.8/10.7/14.5; 131072: 39.7/19.2/
+// 14.3/13.0/15.9).  PSO64_GANG_PPL overrides it.
 static int gang_ppl(uint64_t N)
 {
     if (const char *env = getenv("PSO64_GANG_PPL")) {
@@ -1230,9 +1229,10 @@ namespace {
     } while (0)
 
 // Paths of pso64_run.  The resident gang takes every swarm it accepts and
-// holds (pso_gang64.hip), a held run the larger ones (pso_hold.hip).  Of the
-// others (Cubic, us per iteration): a swarm
-// that the split grid step takes (D >= 32, N <= 32768) runs one grid launch
+// holds (pso_gang64.hip), a held run most larger ones (pso_hold.hip).  The others
+// -- a bound of -0, runs of one or two iterations of a large swarm, N above four
+// million, compute units that another kernel holds -- (Cubic, us per iteration):
+// a swarm that the split grid step takes (D >= 32, N <= 32768) runs one grid launch
 // per iteration (grid / one workgroup: N = 32, D = 120: 8.8 / 31.1; 192, 32:
 // 8.6 / 8.9); else a swarm whose state fits the LDS of one workgroup (x, v, p
 // and pf: about 6 700 particle-dimensions) runs there in one launch; else for

@@ -39,7 +39,8 @@ __device__ __forceinline__ double cospi64(double y)
     const double n = rint(y);
     const double r = y - n;
     const double c = cos(M_PI * r);
-    const double h = 0.5 * n; return h - rint(h) != 0.0 ? -c : c;
+    const double h = 0.5 * n; // an integer iff n is even
+    return h - rint(h) != 0.0 ? -c : c;
 }
 
 // The fitness functions in binary64, accumulated in dimension order.

@@ -127,8 +127,10 @@ struct GangShared {
 };
 
 // PL: dimensions of p kept in LDS, the last of the chunk (large chunks: x, v
-// and p of 64 dimensions are 192 registers of the 256 a lane has at 512 lanes,
-// and spill).  TAIL (Ackley in two chunks of 64: its two words of terms and
+// and p of 64 dimensions are 192 registers of the 256 a lane has at 512 lanes).
+// Several forms spill all the same: at 1024 lanes (128 registers) C = 16 23 to 63
+// registers and C = 8 without whole wavefronts 12 to 20, C = 32 and 64 10 to 22; the
+// shapes below were measured with that.  TAIL (Ackley in two chunks of 64: its two words of terms and
 // p do not both fit LDS): chunk 1's lanes keep their cosines in LDS, and after
 // the barrier continue chunk 0's two sums themselves, their z^2 from x.
 template <int FIT, int C, bool MULTI, bool UNI, bool SPEC, int MAXT, int PL = 0, bool TAIL = false>
@@ -751,9 +753,10 @@ static bool gang_layout(int fitness, const SwarmArgs &a, int cus, int lds_max, i
 // lanes' C dimensions (45 to 60 vector instructions each, all wavefronts of a
 // SIMD in turn), the fold of D - C staged terms (about 8 cycles each) and the
 // meeting (0.9 us for few parts, 1.3 at 128, 2.2 at 256, and 0.5 more where
-// the gbest changed).  Measured on Rastrigin over N = 32 .. 262144 and D = 1
-// .. 300 (the other functions choose alike), us per iteration of the shape
-// taken / the best of the others / the step launches or the one-workgroup run:
+// the gbest changed).  Measured on Rastrigin alone over N = 32 .. 262144 and D = 1
+// .. 300, us per iteration of the shape taken / the best of the others / the step
+// launches or the one-workgroup run; the other functions take the same shapes,
+// except where their settling matters (below):
 //   one part (no meeting; one_part) while its lanes hold the swarm: N = 40, D =
 //     20 1.8 / 2.1 / 2.1; 100, 12 1.85 / 2.6 / 2.24; 257, 5 1.92 / 2.2 / 2.2;
 //     624, 2 1.66 / 1.94 / 1.66 (60 iterations; 0.89 / 0.81 / 1.26 of 300);

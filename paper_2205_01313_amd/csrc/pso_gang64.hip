@@ -608,7 +608,9 @@ static Gang64Kernel gang64_entry()
 template <int FIT>
 static const Gang64Kernel *gang64_table(int *n)
 {
-    // double cos and exp leave 1024 lanes too few registers for C = 8
+    // Double cos and exp leave 1024 lanes too few registers for C = 8; C = 4 spills
+    // there too (42 to 80 registers, without them 6 to 9), C = 8 61 without them, and
+    // C = 32 128 to 148 at 512 lanes (2 to 4 without).
     constexpr int MOST8 = FIT == F_RASTRIGIN || FIT == F_ACKLEY ? 512 : 1024;
     static const Gang64Kernel t[] = {
         gang64_entry<FIT, 1, false, true, true, 1024>(),

@@ -3,8 +3,8 @@
 // the resident gang cannot hold.
 //
 // The grid step moves the whole state through the memory-side cache in every
-// iteration, at the rate a large copy reaches (5.4 TB/s), and that bounds it:
-// the vector instructions take a third to a half of that time.  256 compute units
+// iteration (809 MB at N = 2^20, D = 32, at 6.7 TB/s at the fabric; a large copy
+// 5.4), and that bounds it: the vector instructions take half of that time.  256 compute units
 // hold 128 MiB of registers and 40 MiB of LDS that live as long as a
 // workgroup.  Here a part's 512 lanes each take 16-byte groups of particles
 // (four binary32, two binary64); of a lane's first group, four or five
@@ -23,9 +23,10 @@
 // are the same bits; the cosine, clamps and uniforms take the shorter forms
 // that are exact where gang_accepts says so.
 //
-// Rastrigin, D = 32: N = 2^20, binary32, 200 iterations 24.3 -> 18.1 ms (bound
-// by the three quarters of the state that still stream, at 5.6 TB/s); N = 2^18,
-// binary64, 50 iterations 4.1 -> 2.6 ms (the same, and by the double cosine).
+// Rastrigin, D = 32: N = 2^20, binary32, 200 iterations 24.3 -> 18.0 ms (bound
+// by the three quarters of the state that still stream, 580 MB an iteration at
+// 6.2 to 6.4 TB/s); N = 2^18, binary64, 50 iterations 4.1 -> 2.4 ms (the same, and
+// by the double cosine).
 #include <algorithm>
 #include <cmath>
 #include <cstdlib>
@@ -41,9 +42,13 @@ namespace pso {
 namespace {
 
 constexpr int LANES = 512, LDS_PAIRS_MAX = 3;
-// Pairs held in registers: five, or four beside the double cosine (Rastrigin
-// D = 32, N = 2^18, ms per 50 iterations: 3: 2.65, 4: 2.57, 5: 2.79; binary32,
-// N = 2^20, 200 iterations: 3: 24.2, 4: 18.8, 5: 18.2; six spill).
+// Pairs held in registers: five, or four beside the double cosine.  All forms
+// spill, with five pairs 18 to 26 registers in binary32 and 8 to 14 in binary64,
+// with four beside the cosine 20 and 31, and they are the fastest all the same:
+// D = 32, ms, binary32 N = 2^20, 100 iterations, 3 / 4 / 5 / 6 pairs: Rastrigin 9.95 /
+// 9.60 / 9.33 / 13.1, Sphere 10.0 / 9.73 / 9.48 / 9.61; binary64 N = 2^18, 50
+// iterations, 3 / 4 / 5: Rastrigin 2.33 / 2.33 / 2.49, Ackley 2.34 / 2.33 / 2.57.  Two
+// pairs in LDS instead of three: 9.61 and 2.41.
 template <class T>
 constexpr int held_of(int fitness)
 {

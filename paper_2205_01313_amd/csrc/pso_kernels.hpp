@@ -131,12 +131,12 @@ hipError_t launch_step(int fitness, int variant, const SwarmArgs &a, hipStream_t
 // (PSO_ASYNC_TILES in the environment, 1..64; default 2).
 uint32_t async_tiles_per_workgroup();
 hipError_t launch_arm(const SwarmArgs &a, float tol, float fstar, hipStream_t stream);
-// Clears the gang's rendezvous fields before each gang launch after the first
-// (launch_arm clears them too).
 // Control block and gbest position (if not null) to device-visible pinned host
 // memory; visible to the host once the stream has been synchronised.
 constexpr int FETCH_MAX_D = 4096; // wider positions are for the copy engine
 hipError_t launch_fetch(const SwarmArgs &a, Ctrl *ctrl, float *gpos, hipStream_t stream);
+// Clears the gang's rendezvous fields before each gang launch after the first
+// (launch_arm clears them too).
 hipError_t launch_gang_arm(const SwarmArgs &a, hipStream_t stream);
 // Copies every pending pbest position from x to p (before the state is read).
 hipError_t launch_flush(const SwarmArgs &a, hipStream_t stream);
