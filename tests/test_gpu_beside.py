@@ -70,3 +70,38 @@ def test_runs_of_several_launches_equal_the_step_launches(monkeypatch):
         assert r["gbest_fit"] == r0["gbest_fit"] and r["gbest_iter"] == r0["gbest_iter"]
         for k in st0:
             assert np.array_equal(np.asarray(st[k]), np.asarray(st0[k])), k
+
+
+def test_run_that_finds_the_device_taken_comes_back_to_the_chip():
+    """Matrix products on another stream hold the compute units at first: the
+    parts that are not resident together leave, other launches go on, and once
+    the products are done the run is on the chip again; held and resident."""
+    import torch
+
+    import paper_2205_01313_amd as pso
+
+    a = torch.randn(8192, 8192, device="cuda", dtype=torch.bfloat16)
+    side = torch.cuda.Stream()
+    for spec, make, path in ((wl.SwarmSpec("rastrigin", 262144, 30, 12000, seed=9), gpu_swarm, "resident"),
+                             (wl.SwarmSpec("sphere", 1 << 19, 48, 2500, seed=3), gpu_swarm, "held"),
+                             (wl.SwarmSpec("cubic", 16384, 100, 10000, seed=4), None, "resident")):
+        announce(f"beside matrix products: {spec.fitness} N={spec.N} D={spec.D}")
+        if make is None:
+            g = pso.Swarm64(spec.fitness, spec.N, spec.D, spec.box, spec.w, spec.c1, spec.c2, spec.vmax, spec.seed)
+        else:
+            g = make(spec)
+        with g:
+            alone = g.run(spec.T)
+            g.reset()
+            torch.cuda.synchronize()
+            with torch.cuda.stream(side):
+                for _ in range(40):
+                    b = a @ a
+            r = g.run(spec.T)
+            n = g.run_paths()
+            torch.cuda.synchronize()
+            print(f"paths {n}", flush=True)
+        assert sum(n.values()) == 2 * spec.T and n[path] >= spec.T + spec.T // 4
+        assert r["gbest_fit"] == alone["gbest_fit"] and r["gbest_iter"] == alone["gbest_iter"]
+        assert np.array_equal(r["gbest_pos"], alone["gbest_pos"])
+    assert torch.equal(b, a @ a)
