@@ -806,10 +806,12 @@ bool gang_shape(int fitness, const SwarmArgs &a, int64_t t0, int64_t T, GangShap
     if (fitness == F_ACKLEY && D <= 2 && N > 384 && N <= 1024 && end < 200) return false;
     // A brief run stays in one part longer (settles_late; us of 200 iterations, one
     // part / more: Rosenbrock D = 3, N = 800 400 / 490; Rastrigin D = 2, N = 641
-    // 203 / 196, of 100 137 / 146; Sphere D = 2, N = 641 of 600 621 / 697).
+    // 203 / 196, of 100 137 / 146; Sphere D = 2, N = 641 of 600 621 / 697; Rosenbrock
+    // D = 10, N = 343 of 300 818 / 919, D = 12, N = 500 864 / 950).
     const bool brief = end < 200, longer = late && end < 800;
     const uint32_t most2 = brief ? 1024 : longer && D == 2 ? 768 : 640, most4 = brief || longer ? 960 : 768;
-    if (one_part(N, D, most2, most4, 256, [&](int c, uint32_t P) { return layout(c, P, out); })) return true;
+    const uint32_t most8 = longer && D <= 12 ? 512 : 256;
+    if (one_part(N, D, most2, most4, most8, [&](int c, uint32_t P) { return layout(c, P, out); })) return true;
     // Several parts: the state's way in and out of the registers and the
     // rendezvous of up to 256 parts have to pay.  Against the step launches (us of
     // a run of T, here / there): N = 4000, D = 30 T = 1 35 / 29, 2 39 / 39; N =

@@ -258,3 +258,12 @@ def test_stopped_gang_keeps_the_pending_marks(monkeypatch, fit, N, D, shape):
         assert out[0]["t"] == out[1]["t"] == 4
         for k in ("x", "v", "p", "pf"):
             assert np.array_equal(out[0][k].view(bits), out[1][k].view(bits)), k
+
+
+@pytest.mark.parametrize("fit,N,D", [("rosenbrock", 343, 10), ("sphere", 512, 12), ("rosenbrock", 511, 9)])
+def test_one_part_of_eight_dimensions_a_lane(fit, N, D):
+    """Sizes that take one part of wide chunks while they settle, and several
+    parts once the run ends later."""
+    spec = wl.SwarmSpec(fit, N, D, 900, seed=N + D, shift_amplitude=1.0)
+    announce(f"one part {fit} N={N} D={D}")
+    check(spec, (60, 840))
