@@ -438,7 +438,7 @@ typedef struct pso_server_counters {
  * keep its state in registers (PSO_BATCH_REGISTERS=0 in the environment: none)
  * or in LDS while they last, by size and by the requests in flight, others in
  * streamed ones; a launch is of one kind and takes the longest-waiting ready
- * swarms of that kind, at most 8 parts per workgroup (PSO_SERVER_STAGED=0 in
+ * swarms of that kind, at most 4 parts per workgroup (PSO_SERVER_STAGED=0 in
  * the environment streams every request). */
 int pso_server_create(size_t mem_budget, int64_t chunk_updates, pso_server **out);
 
