@@ -823,7 +823,8 @@ bool gang_shape(int fitness, const SwarmArgs &a, int64_t t0, int64_t T, GangShap
     // 3, of the steps' time: N = 36000 1.25 and 1.03, N = 97000 1.55 and 1.21; Sphere
     // 0.96 and 0.77, 0.67 and 0.54).
     const bool light = fitness == F_RASTRIGIN || fitness == F_CUBIC;
-    int64_t shortest = N <= 65536 ? (D > 16 ? 2 : 1) : D <= 4 ? 8 : D <= 16 ? (N > 131072 ? 6 : 4) : (N > 131072 ? 4 : 2);
+    const bool most = N > 131072;
+    int64_t shortest = N <= 65536 ? (D > 16 ? 2 : 1) : D <= 4 ? (most ? 10 : 8) : D <= 16 ? (most ? 6 : 4) : (most ? 4 : 2);
     if (light && D > 16 && N > 24000) shortest = N > 65536 ? 5 : 4;
     if (T < shortest) return false;
     int c = D == 1 ? 1 : 2;
