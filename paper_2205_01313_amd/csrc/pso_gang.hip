@@ -817,7 +817,8 @@ bool gang_shape(int fitness, const SwarmArgs &a, int64_t t0, int64_t T, GangShap
     // a run of T, here / there): N = 4000, D = 30 T = 1 35 / 29, 2 39 / 39; N =
     // 131072: D = 2 T = 1 59 / 26, 4 65 / 49, 8 70 / 74; D = 16 T = 2 63 / 50, 4 66 /
     // 78; D = 30 T = 1 80 / 51, 2 84 / 92; N = 262144: D = 1 T = 4 90 / 56, 8 100 / 93;
-    // D = 8 T = 4 102 / 79, 6 110 / 106; D = 30 T = 2 129 / 95, 4 155 / 165.  Up to
+    // D = 8 T = 4 102 / 79, 6 110 / 106; D = 30 T = 2 129 / 95, 4 155 / 165 (its runs of
+    // eight and nine at D <= 4 are held, level with the steps: 93 / 92).  Up to
     // N = 65536 one iteration of D <= 16 is level with the steps.  Rastrigin and
     // Cubic improve fewer pbests early on, which the steps gain from (D = 43, T = 2 and
     // 3, of the steps' time: N = 36000 1.25 and 1.03, N = 97000 1.55 and 1.21; Sphere
