@@ -75,7 +75,7 @@ size_t gang_words(uint32_t parts, int D);
 // Sphere and Rosenbrock go down one valley and improve their gbest in most of
 // the first 500 to 1000 iterations, where the others settle after 100 to 200.
 // Every change is a meeting, so while it lasts fewer parts are better.
-inline bool settles_late(int fitness) { return fitness == 0 || fitness == 2; }
+inline bool settles_late(int fitness) { return fitness == 0 || fitness == 2; } // PSO_SPHERE, PSO_ROSENBROCK
 // A swarm small enough for one part: layout(C, P) with its particles packed
 // (whole wavefronts where a lane holds a particle) and the smallest chunk that
 // fits, from C = 4 on for D > 12, whose fold is shorter that way.  most2, most4

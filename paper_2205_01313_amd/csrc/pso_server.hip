@@ -111,8 +111,9 @@ constexpr int MAX_SERVER_D = 4096; // LDS of a launch is sized for the largest D
 // kind, and a request of the kind that the other stream runs waits for that launch
 // (five requests of N = 287 to 1150, D = 10 to 20, 130 iterations: 1030 us of one
 // kind, 1590 of two; 80 random bursts of 1 to 120 requests take 0.91 of the time
-// they took when LDS held all of them, 0.97 with each request's own kind).  Independent arrivals are further
-// apart and keep their own: p50 at 2000 requests/s 5.12 ms, 5.25 with 0.2 ms here.
+// they took when LDS held all of them, 0.97 with each request's own kind).
+// Independent arrivals are further apart and keep their own: p50 at 2000 requests/s
+// 5.12 ms, 5.25 with 0.2 ms here.
 constexpr double BURST_MS = 0.05;
 constexpr uint64_t BURST_MOST = 32;
 constexpr int SERVER_STAGE_LANES = 1024;
@@ -749,7 +750,8 @@ int pso_server_submit(pso_server *s, const pso_desc *d, uint64_t *ticket)
         {
             std::lock_guard<std::mutex> g(s->mu);
             in_flight = s->submitted - s->completed - s->rejected - s->cancelled - s->timed_out;
-            if (in_flight > 0 && in_flight < BURST_MOST && ms_since(s->last_submit, r->t_submit) < BURST_MS) burst_kind = s->last_kind;
+            if (in_flight > 0 && in_flight < BURST_MOST && ms_since(s->last_submit, r->t_submit) < BURST_MS)
+                burst_kind = s->last_kind;
         }
         uint32_t parts[KINDS] = {};
         for (int kind : {STAGED, REGISTERS})
